@@ -7,35 +7,31 @@
 
 namespace dsm {
 
-// Elements per work-group chunk.  A chunk never crosses a tensor boundary,
-// so the per-tensor facts a kernel needs (decay flag, tensor index for the
-// randomized sign's bound and Philox counter) are uniform per work-group and
-// read once.  Multiple of 4 (float4) and of 256 threads x 4.
-#ifndef DSM_CHUNK_ELEMS
-#define DSM_CHUNK_ELEMS 16384
-#endif
-constexpr int kChunkElems = DSM_CHUNK_ELEMS;
-static_assert(kChunkElems % 1024 == 0, "chunk must be a multiple of 256 threads x 4");
-#ifndef DSM_BLOCK_THREADS
-#define DSM_BLOCK_THREADS 256
-#endif
-constexpr int kBlockThreads = DSM_BLOCK_THREADS;
-static_assert(kBlockThreads % 64 == 0 && kBlockThreads <= 1024, "whole waves, at most 1024 threads");
-// float4 groups per stream in flight per thread, and loop iterations per
-// work-group: a work-group takes one piece of kBlockThreads * kUnroll *
-// kIters float4 groups of a chunk (build-time tuning knobs).
-#ifndef DSM_UNROLL
-#define DSM_UNROLL 1
-#endif
-#ifndef DSM_ITERS
-#define DSM_ITERS 1
-#endif
-constexpr int kUnroll = DSM_UNROLL;
-constexpr int kIters = DSM_ITERS;
-constexpr int kPieceVec = kBlockThreads * kUnroll * kIters;
-static_assert((kChunkElems / 4) % kPieceVec == 0, "a chunk must split into whole pieces");
-// Work-groups per chunk.
-constexpr int kSplit = (kChunkElems / 4) / kPieceVec;
+// Elements per chunk.  A chunk never crosses a tensor boundary, so the
+// per-tensor facts a kernel needs (decay flag, tensor index for the randomized
+// sign's bound and Philox counter) are uniform per wave and read once.
+constexpr int kChunkElems = 16384;
+// A wave takes one strip of a chunk per stream: 64 lanes x one float4.  Eight
+// strips, one per XCD, are a strip group.
+constexpr int kWave = 64;
+constexpr int kAllWaves = 32;  // waves a CU holds
+constexpr int kXcds = 8;       // MI355X: work-groups go to its 8 XCDs round-robin
+constexpr int kStripVec = kWave;
+constexpr int kStrips = kChunkElems / 4 / kStripVec;  // strips per chunk
+constexpr int kGroupStrips = kXcds;
+constexpr int kGroupElems = 4 * kStripVec * kGroupStrips;
+static_assert(kChunkElems % kGroupElems == 0, "a chunk must split into whole strip groups");
+// Work-groups of four waves (quads), and the 1024-element pieces of a chunk,
+// each with one word of the randomized sign's bound.
+constexpr int kQuadWaves = 4;
+constexpr int kBlockThreads = kQuadWaves * kWave;
+constexpr int kUnroll = 1;  // float4 groups per stream of a thread of a piece
+constexpr int kPieceVec = kBlockThreads * kUnroll;
+constexpr int kSplit = kChunkElems / 4 / kPieceVec;  // pieces per chunk
+constexpr int kGroupPieces = kGroupStrips / kQuadWaves;
+static_assert(kSplit % kXcds == 0, "the strips of a quad must lie in one chunk");
+// Most waves of a work-group of the fused round end (more workers share them).
+constexpr int kMaxRoundEndWaves = 16;
 // Arena alignment of every tensor, in elements (256 bytes).
 constexpr int64_t kTensorAlign = 64;
 constexpr int kMaxWorkers = 64;
@@ -43,7 +39,7 @@ constexpr int kMaxWorkers = 64;
 // Replica buffers in 64 KiB blocks (dsm_problem.replica_layout =
 // DSM_REPLICAS_BLOCKED): copy i of block b sits at element (b * n + i) *
 // kRepBlockElems.  Tensors then start on a multiple of the piece size (and of
-// 1024 elements), so a work-group's piece never crosses a block, and the
+// 1024 elements), so a wave's strip never crosses a block, and the
 // arena length is a whole number of blocks.
 constexpr int kRepBlockShift = 14;
 constexpr int64_t kRepBlockElems = int64_t(1) << kRepBlockShift;
@@ -57,8 +53,19 @@ struct RepLayout {
     int64_t block_stride;
     int64_t copy_stride;
     int32_t shift;
-    int32_t pad;
+    // Of the problem, not of the buffer: 0, or where most strip groups of its
+    // chunks hold no elements (many tensors far shorter than a chunk), the
+    // number of those that do; its launches then go over these only.
+    int32_t groups;
 };
+// Sparse from half the groups empty on.  A wave of a sparse launch searches for
+// its chunk, ~1 us; the waves it saves cost their dispatch (125 tensors of 64K
+// elements in all, n = 16, 25 times as many empty groups as full ones: a fused
+// round takes 72 us, 142 us before; 400 tensors, 43% of the groups hold
+// elements: 81 us, 86 us before).
+constexpr bool sparse_chunks(int64_t groups, int64_t n_chunks) {
+    return 2 * groups <= n_chunks * (kStrips / kGroupStrips);
+}
 // n contiguous copies of d_pad elements.
 inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0}; }
 // n copies interleaved in 64 KiB blocks.
@@ -94,7 +101,7 @@ struct Chunk {
     int32_t len;      // elements in the chunk, 1..kChunkElems
     uint32_t tensor;  // tensor index p
     uint32_t decay;   // 1 if weight decay applies to the tensor
-    uint32_t pad;
+    uint32_t group0;  // strip groups of the chunks before this one that hold elements
 };
 static_assert(sizeof(Chunk) == 32, "chunk descriptor is 32 bytes");
 
@@ -135,7 +142,7 @@ struct GlobalScalars {
 // index itself (XCD k takes piece k mod 8 of every chunk); 1, XCD k takes the
 // k-th eighth of the grid row, in order; 2, XCD k takes whole chunks.  The
 // best map of each kernel kind depends on the replica layout (measured), so
-// the runtime keeps one set per layout; build-time -D settings override them.
+// the runtime keeps one set per layout; the fused round end go over strips instead, and take 0.
 // global: the global steps and the randomized second pass of the round end;
 // copy: the broadcast of dsm_sync and the initial copy of dsm_init.
 //
@@ -144,20 +151,18 @@ struct GlobalScalars {
 // piece of successive workers (with the state blocked, one block at a time)
 // instead of running worker by worker.
 constexpr int kInterleaveWorkers = 4;
+constexpr int kQuads = 8;  // work-groups of four waves
 struct XcdMaps {
     int local, round_end, from_x, global, copy;
 };
-#ifndef DSM_MAPS_CONTIGUOUS
-#define DSM_MAPS_CONTIGUOUS 1, 2, 2, 0, 0
-#endif
-#ifndef DSM_MAPS_BLOCKED
-#define DSM_MAPS_BLOCKED 1, 2, 1, 0, 1
-#endif
-#ifndef DSM_MAPS_STATE_BLOCKED
-#define DSM_MAPS_STATE_BLOCKED 1 + kInterleaveWorkers, 1, 1, 1, 1
-#endif
-constexpr XcdMaps kMapsByLayout[3] = {{DSM_MAPS_CONTIGUOUS}, {DSM_MAPS_BLOCKED},
-                                      {DSM_MAPS_STATE_BLOCKED}};
+constexpr XcdMaps kMapsByLayout[3] = {{1, 0, 2, 0, 0}, {1, 0, 1, 0, 1}, {1 + kInterleaveWorkers, 0, 1, 1, 1}};
+
+// How a kernel finds its strips: the launch map, and the number of chunks when
+// it goes over the strip groups that hold elements (RepLayout::groups), else 0.
+struct Rows {
+    int32_t map;
+    uint32_t sparse_chunks;
+};
 
 // The map a local step over n_workers workers launches with: the interleaved
 // order needs the whole pieces x workers row in one grid dimension, which

@@ -26,28 +26,11 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-// Whether the streams use nontemporal loads and stores, and how far the
-// fused round end unrolls its worker loop (build-time knobs).
-#ifndef DSM_NT
-#define DSM_NT 1
-#endif
-#ifndef DSM_ROUND_END_UNROLL
-#define DSM_ROUND_END_UNROLL 0
-#endif
-
 __device__ __forceinline__ f4 ntload(const f4* p) {
-#if DSM_NT
     return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
 }
 __device__ __forceinline__ void ntstore(f4 v, f4* p) {
-#if DSM_NT
     __builtin_nontemporal_store(v, p);
-#else
-    *p = v;
-#endif
 }
 
 // Stores the first k (1..3) lanes of v: the ragged end of a tensor.
@@ -91,8 +74,6 @@ struct Piece {
     int64_t e0;      // arena element of the piece's first group
     uint32_t j4;     // in-tensor index of the first group, divided by 4
 };
-
-constexpr uint32_t kXcds = 8;  // MI355X: work-groups go to its 8 XCDs round-robin
 
 // Work item of this work-group.  MAP 0: the work-group index itself (XCD k
 // takes piece k mod 8 of every chunk).  1: XCD k takes the k-th eighth of the
@@ -154,6 +135,84 @@ __device__ __forceinline__ Piece local_piece(const Chunk* __restrict__ chunks, i
     }
     w = worker0 + static_cast<int64_t>(blockIdx.y);
     return piece_at(chunks, work_index(map & 3));
+}
+
+// ---------------------------------------------------------------- strips
+
+// A strip of a chunk: 64 consecutive float4 groups, one per lane of a wave
+// (fewer at the chunk's end, none past it).  Wave-uniform.
+struct Strip {
+    Chunk c;
+    int nq;          // float4 groups in the strip
+    int valid0;      // lanes of the chunk from the strip's first group on
+    int64_t e0;      // arena element of the strip's first group
+    uint32_t j4;     // in-tensor index of the first group, divided by 4
+    uint32_t piece;  // the 1024-element piece the strip lies in
+};
+
+__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+__device__ __forceinline__ int wave_id() {
+    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+// The chunk that holds strip group g (Chunk.group0 ascends over the chunks):
+// a 64-ary search by the whole wave, one gather per factor of 64 in the
+// number of chunks.
+__device__ __forceinline__ uint32_t find_chunk(const Chunk* __restrict__ chunks, uint32_t n_chunks,
+                                               uint32_t g) {
+    uint32_t lo = 0, size = n_chunks;
+    while (size > 1) {
+        const uint32_t step = (size + 63) / 64, at = static_cast<uint32_t>(lane_id()) * step;
+        const bool at_or_below = at < size && chunks[lo + min(at, size - 1)].group0 <= g;
+        const uint32_t k = static_cast<uint32_t>(__popcll(__ballot(at_or_below))) - 1;
+        lo += k * step;
+        size = min(step, size - k * step);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Strip si of a launch: of all chunks' kStrips each, or (rows.sparse_chunks
+// > 0) of the strip groups that hold elements.
+__device__ __forceinline__ Strip strip_at(const Chunk* __restrict__ chunks, const Rows& rows,
+                                          uint32_t si) {
+    uint32_t ci = si / kStrips, s = si % kStrips;
+    if (rows.sparse_chunks > 0) {
+        ci = find_chunk(chunks, rows.sparse_chunks, si / kGroupStrips);
+        s = si - chunks[ci].group0 * kGroupStrips;
+    }
+    Strip st;
+    st.c = chunks[ci];
+    const int nvec = (st.c.len + 3) >> 2;
+    const int q_lo = static_cast<int>(s) * kStripVec;
+    st.nq = max(0, min(nvec - q_lo, kStripVec));
+    st.valid0 = st.c.len - 4 * q_lo;
+    st.e0 = st.c.off + 4 * static_cast<int64_t>(q_lo);
+    st.j4 = static_cast<uint32_t>(st.c.j0 >> 2) + static_cast<uint32_t>(q_lo);
+    st.piece = ci * kSplit + s / kQuadWaves;
+    return st;
+}
+
+// Strip k (0..3) of work-group b of a launch over pieces (quads): strip
+// b % 8 + 8 k of the 32 strips of work-groups 8 (b / 8) to 8 (b / 8) + 7, so
+// that the XCDs, which get the work-groups in turn, interleave at 1 KiB as
+// with one-strip work-groups; over sparse chunks, whose neighbouring strip
+// groups may lie in different tensors, four consecutive strips.
+__device__ __forceinline__ Strip quad_strip(const Chunk* __restrict__ chunks, const Rows& rows,
+                                            int k) {
+    const uint32_t b = blockIdx.x, uk = static_cast<uint32_t>(k);
+    if (rows.sparse_chunks > 0) return strip_at(chunks, rows, b * kQuadWaves + uk);
+    return strip_at(chunks, rows, b / kXcds * (kXcds * kQuadWaves) + uk * kXcds + b % kXcds);
+}
+
+// The strip of this wave: of a one-wave work-group, or of a quad of four.
+__device__ __forceinline__ Strip strip_of(const Chunk* __restrict__ chunks, const Rows& rows) {
+    if (rows.map & kQuads) return quad_strip(chunks, rows, wave_id());
+    return strip_at(chunks, rows, blockIdx.x);
+}
+
+// The bound word of work-group b of a quad launch.
+__device__ __forceinline__ uint32_t quad_word(const Strip& st, const Rows& rows) {
+    return rows.sparse_chunks > 0 ? st.piece : blockIdx.x;
 }
 
 // ---------------------------------------------------------------- AdamW
@@ -419,24 +478,38 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_det(
     }
 }
 
-// Largest of the values of a work-group of THREADS threads, valid in thread
-// 0.  wave_max holds THREADS / 64 words of LDS.
-template <int THREADS>
-__device__ __forceinline__ uint32_t block_max(uint32_t bits, uint32_t* wave_max) {
+// Largest of a wave's values, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t bits) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         const uint32_t o = __shfl_xor(bits, off, 64);
         bits = o > bits ? o : bits;
     }
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    if (lane == 0) wave_max[wave] = bits;
+    return bits;
+}
+
+// Largest of the values of a work-group of THREADS threads, valid in thread
+// 0.  lds holds THREADS / 64 words of LDS.
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_max(uint32_t bits, uint32_t* lds) {
+    bits = wave_max(bits);
+    if (lane_id() == 0) lds[threadIdx.x >> 6] = bits;
     __syncthreads();
-    uint32_t b = wave_max[0];
+    uint32_t b = lds[0];
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int w = 1; w < THREADS / 64; ++w) b = wave_max[w] > b ? wave_max[w] : b;
+        for (int w = 1; w < THREADS / 64; ++w) b = lds[w] > b ? lds[w] : b;
     }
+    return b;
+}
+
+// Largest |u| of the first `valid` lanes, as a bit pattern (for non-negative
+// IEEE floats the unsigned order of the bit patterns is the numeric order).
+__device__ __forceinline__ uint32_t abs_max(f4 u, int valid) {
+    uint32_t b = __float_as_uint(fabsf(u.x));
+    if (valid > 1) b = max(b, __float_as_uint(fabsf(u.y)));
+    if (valid > 2) b = max(b, __float_as_uint(fabsf(u.z)));
+    if (valid > 3) b = max(b, __float_as_uint(fabsf(u.w)));
     return b;
 }
 
@@ -445,9 +518,8 @@ __device__ __forceinline__ uint32_t block_max(uint32_t bits, uint32_t* wave_max)
 // |u| of its piece, as a bit pattern, in the piece's own slot (for
 // non-negative IEEE floats the unsigned order of the bit patterns is the
 // numeric order).  Level two is k_bound_reduce.
-__device__ __forceinline__ void store_piece_max(uint32_t bits, uint32_t* wave_max,
-                                                uint32_t* slot) {
-    const uint32_t b = block_max<kBlockThreads>(bits, wave_max);
+__device__ __forceinline__ void store_piece_max(uint32_t bits, uint32_t* lds, uint32_t* slot) {
+    const uint32_t b = block_max<kBlockThreads>(bits, lds);
     if (threadIdx.x == 0) *slot = b;
 }
 
@@ -462,7 +534,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
     const f4* __restrict__ xp = reinterpret_cast<const f4*>(x + pc.e0);
     f4* __restrict__ mp = reinterpret_cast<f4*>(m + pc.e0);
     f4* __restrict__ up = reinterpret_cast<f4*>(u_out + pc.e0);
-    __shared__ uint32_t wave_max[kBlockThreads / 64];
+    __shared__ uint32_t lds[kBlockThreads / 64];
     uint32_t maxbits = 0;
     for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
         f4 xv[kUnroll], mv[kUnroll], dv[kUnroll];
@@ -495,35 +567,37 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
             }
         }
     }
-    store_piece_max(maxbits, wave_max, piece_max + pc.wi);
+    store_piece_max(maxbits, lds, piece_max + pc.wi);
 }
 
-// Level two of the tensor bound: work-group p takes the piece maxima of
-// tensor p (slots chunk0[p] * kSplit up to chunk0[p + 1] * kSplit, the pieces
-// of its chunks) and stores their largest in bound_bits[p]; an empty tensor
-// has no slots and gets 0.
+// Level two of the tensor bound: work-group p takes the level-one words of
+// tensor p, kSplit for each of its chunks from chunk0[p] * kSplit on, and
+// stores their largest in bound_bits[p]; an empty tensor has none and gets 0.
+// Over sparse chunks only the words of the strip groups that hold elements
+// have been written: a prefix, since all chunks of a tensor but the last are
+// full.
 constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void k_bound_reduce(
-    const uint32_t* __restrict__ piece_max, const int32_t* __restrict__ chunk0,
-    uint32_t* __restrict__ bound_bits) {
-    __shared__ uint32_t wave_max[kReduceThreads / 64];
+    const Chunk* __restrict__ chunks, const uint32_t* __restrict__ piece_max,
+    const int32_t* __restrict__ chunk0, uint32_t* __restrict__ bound_bits, bool sparse) {
+    __shared__ uint32_t lds[kReduceThreads / 64];
     const int p = blockIdx.x;
-    const int64_t lo = static_cast<int64_t>(chunk0[p]) * kSplit;
-    const int64_t hi = static_cast<int64_t>(chunk0[p + 1]) * kSplit;
+    const int32_t c_lo = chunk0[p], c_hi = chunk0[p + 1];
+    const int64_t lo = static_cast<int64_t>(c_lo) * kSplit;
+    int64_t n = static_cast<int64_t>(c_hi - c_lo) * kSplit;
+    if (sparse && n > 0)
+        n -= kSplit - (chunks[c_hi - 1].len + kGroupElems - 1) / kGroupElems * kGroupPieces;
     uint32_t b = 0;
-    if constexpr (kSplit % 4 == 0) {
-        // lo is a multiple of 4 slots, and the slots start 256-byte aligned.
-        const uint4* __restrict__ v = reinterpret_cast<const uint4*>(piece_max + lo);
-        const int64_t nv = (hi - lo) / 4;
+    // lo is a multiple of 4 slots, and the slots start 256-byte aligned.
+    const uint4* __restrict__ v = reinterpret_cast<const uint4*>(piece_max + lo);
 #pragma unroll 4
-        for (int64_t i = threadIdx.x; i < nv; i += kReduceThreads) {
-            const uint4 w = v[i];
-            b = max(b, max(max(w.x, w.y), max(w.z, w.w)));
-        }
-    } else {
-        for (int64_t i = lo + threadIdx.x; i < hi; i += kReduceThreads) b = max(b, piece_max[i]);
+    for (int64_t i = threadIdx.x; i < n / 4; i += kReduceThreads) {
+        const uint4 w = v[i];
+        b = max(b, max(max(w.x, w.y), max(w.z, w.w)));
     }
-    b = block_max<kReduceThreads>(b, wave_max);
+    const int64_t i = n / 4 * 4 + threadIdx.x;
+    if (i < n) b = max(b, piece_max[lo + i]);
+    b = block_max<kReduceThreads>(b, lds);
     if (threadIdx.x == 0) bound_bits[p] = b;
 }
 
@@ -623,13 +697,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_local_from_x(
             const int q = q0 + k * kBlockThreads;
             if (q < pc.nq) xv[k] = ntload(xp + q);
         }
-#if DSM_ROUND_END_UNROLL == 0
 #pragma unroll(N > 0 ? N : 1)
-#elif DSM_ROUND_END_UNROLL == 1
-#pragma unroll 1
-#elif DSM_ROUND_END_UNROLL == 2
-#pragma unroll 2
-#endif
         for (int i = 0; i < (N > 0 ? N : n); ++i) {
             f4* __restrict__ xr = reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0));
             const f4* __restrict__ gp = reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, pc.e0));
@@ -669,118 +737,105 @@ __global__ __launch_bounds__(kBlockThreads) void k_local_from_x(
 
 // The last local step of every worker (Algorithm 2 or 3, Eq. (4)) fused with
 // the global step (all-reduce, Eqs. (6)-(8)): each worker's step-H replica
-// value stays in registers and is folded into the worker-order sum
-// sum_i (x - x_i) as it is produced, so the replicas are neither stored after
-// step H nor read back.  Per element the operations and their order are those
-// of k_local_* followed by k_global_det / k_global_rand_pass1, so the results
-// are bit-identical.  KIND: 0 deterministic sign, 1 deterministic sign with
+// value stays on the CU and is folded into the worker-order sum
+// sum_i (x - x_i), so the replicas are neither stored after step H nor read
+// back.  Per element the operations and their order are those of k_local_*
+// followed by k_global_det / k_global_rand_pass1, so the results are
+// bit-identical.  KIND: 0 deterministic sign, 1 deterministic sign with
 // broadcast, 2 randomized pass 1 (u, m and the bound; pass 2 follows).
-
-template <int N, int BASE, int KIND>
-__global__ __launch_bounds__(kBlockThreads) void k_round_end(
-    const Chunk* __restrict__ chunks, int map, float* x, float* __restrict__ m, float* x_rep,
+//
+// A strip's workers are spread over `workers` waves of a work-group, which
+// leave their step-H values in LDS for the first of them to do the global
+// step.  PIECE false: a work-group takes one strip (KIND 2: and raises its
+// bound word by an atomic max).  PIECE true (KIND 2): it takes the four strips
+// of a bound word side by side and stores the word.
+template <int BASE, int KIND, bool PIECE>
+__global__ __launch_bounds__(kMaxRoundEndWaves * kWave) void k_round_end(
+    const Chunk* __restrict__ chunks, Rows rows, float* x, float* __restrict__ m, float* x_rep,
     RepLayout rl, const float* x_src, RepLayout sl, const float* __restrict__ g_rep,
     float* __restrict__ s1, float* __restrict__ s2, float* __restrict__ u_out,
-    uint32_t* __restrict__ piece_max, StateLayout ml, AdamScalars as, SgdScalars ss,
+    uint32_t* __restrict__ piece_max, StateLayout ml, int workers, AdamScalars as, SgdScalars ss,
     GlobalScalars gs) {
     // x_src is the replicas or, when they are stale, x itself: it may alias
     // x and x_rep, so none of the three is __restrict__.  Every load of a
     // group precedes its stores.
-    __shared__ uint32_t wave_max[kBlockThreads / 64];
-    const Piece pc = piece_of(chunks, map);
-    const int n = N > 0 ? N : gs.n;
-    f4* xp = reinterpret_cast<f4*>(x + pc.e0);
-    f4* __restrict__ mp = reinterpret_cast<f4*>(m + pc.e0);
-    const float lam_local = pc.c.decay ? as.wd : 0.0f;
-    const float lam = pc.c.decay ? gs.lam : 0.0f;
+    extern __shared__ f4 x_end[];  // [strips][n][64]: step-H values
+    const int q = lane_id();
+    const int k = PIECE ? wave_id() / workers : 0;  // which of the strips
+    const int w0 = PIECE ? wave_id() % workers : wave_id();
+    f4* const ends = x_end + k * gs.n * kWave + q;
+    const Strip st = PIECE ? quad_strip(chunks, rows, k) : strip_at(chunks, rows, blockIdx.x);
     uint32_t maxbits = 0;
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], mv[kUnroll], acc[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xp + q);
-                mv[k] = ntload(mp + q);
-            }
+    const bool on = q < st.nq;
+    const int valid = st.valid0 - 4 * q;
+    f4* xp = reinterpret_cast<f4*>(x + st.e0) + q;
+    f4* __restrict__ mp = reinterpret_cast<f4*>(m + st.e0) + q;
+    f4 xv, mv;
+    if (w0 == 0 && on) {
+        xv = ntload(xp);
+        mv = ntload(mp);
+    }
+    const float lam_local = st.c.decay ? as.wd : 0.0f;
+    for (int i = w0; i < gs.n && on; i += workers) {
+        f4* __restrict__ s1p = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, st.e0)) + q;
+        f4 xi = ntload(reinterpret_cast<const f4*>(x_src + rep_index(sl, i, st.e0)) + q);
+        const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, st.e0)) + q);
+        f4 mi = ntload(s1p);
+        if (BASE == kBaseAdamW) {
+            f4* __restrict__ s2p = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, st.e0)) + q;
+            f4 vi = ntload(s2p);
+            adamw4(xi, g, mi, vi, lam_local, as);
+            store_vec(vi, s2p, valid);
+        } else {
+            sgdm4(xi, g, mi, ss);
         }
-        // Worker loop: unrolled DSM_ROUND_END_UNROLL workers at a time (0: fully,
-        // for a compile-time worker count).  Fully unrolled, every worker's loads
-        // are in flight together; that measured faster than the rolled loop's
-        // lower register count and higher occupancy.
-#if DSM_ROUND_END_UNROLL == 0
-#pragma unroll(N > 0 ? N : 1)
-#elif DSM_ROUND_END_UNROLL == 1
-#pragma unroll 1
-#elif DSM_ROUND_END_UNROLL == 2
-#pragma unroll 2
-#endif
-        for (int i = 0; i < (N > 0 ? N : n); ++i) {
-            const f4* xs = reinterpret_cast<const f4*>(x_src + rep_index(sl, i, pc.e0));
-            const f4* __restrict__ gp = reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, pc.e0));
-            f4* __restrict__ s1p = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, pc.e0));
-            f4* __restrict__ s2p = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, pc.e0));
-            f4 xi[kUnroll], gi[kUnroll], mi[kUnroll], vi[kUnroll];
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k) {
-                const int q = q0 + k * kBlockThreads;
-                if (q < pc.nq) {
-                    xi[k] = ntload(xs + q);
-                    gi[k] = ntload(gp + q);
-                    mi[k] = ntload(s1p + q);
-                    if (BASE == kBaseAdamW) vi[k] = ntload(s2p + q);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k) {
-                const int q = q0 + k * kBlockThreads;
-                if (q < pc.nq) {
-                    const int valid = pc.valid0 - 4 * q;
-                    if (BASE == kBaseAdamW) {
-                        adamw4(xi[k], gi[k], mi[k], vi[k], lam_local, as);
-                        store_vec(vi[k], s2p + q, valid);
-                    } else {
-                        sgdm4(xi[k], gi[k], mi[k], ss);
-                    }
-                    store_vec(mi[k], s1p + q, valid);
-                    const f4 d = xv[k] - xi[k];
-                    acc[k] = (i == 0) ? d : acc[k] + d;
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                const int valid = pc.valid0 - 4 * q;
-                f4 delta;
-                if (N > 0 || gs.n_pow2)
-                    delta = acc[k] * gs.inv_n;
-                else
-                    delta = acc[k] / gs.n_f;
-                const f4 u = momentum4(mv[k], delta, gs);
-                store_vec(mv[k], mp + q, valid);
-                if (KIND == 2) {
-                    store_vec(u, reinterpret_cast<f4*>(u_out + pc.e0) + q, valid);
-                    uint32_t b = __float_as_uint(fabsf(u.x));
-                    if (valid > 1) b = max(b, __float_as_uint(fabsf(u.y)));
-                    if (valid > 2) b = max(b, __float_as_uint(fabsf(u.z)));
-                    if (valid > 3) b = max(b, __float_as_uint(fabsf(u.w)));
-                    maxbits = max(maxbits, b);
-                } else {
-                    const f4 xn = model4(xv[k], sign4(u), lam, gs);
-                    store_vec(xn, xp + q, valid);
-                    if (KIND == 1) {
-                        for (int i = 0; i < n; ++i)
-                            store_vec(xn,
-                                      reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0)) + q,
-                                      valid);
-                    }
-                }
+        store_vec(mi, s1p, valid);
+        ends[i * kWave] = xi;
+    }
+    __syncthreads();
+    if (w0 == 0 && on) {
+        f4 acc = xv - ends[0];
+        for (int i = 1; i < gs.n; ++i) acc = acc + (xv - ends[i * kWave]);
+        const f4 delta = gs.n_pow2 ? acc * gs.inv_n : acc / gs.n_f;
+        const f4 u = momentum4(mv, delta, gs);
+        store_vec(mv, mp, valid);
+        if (KIND == 2) {
+            store_vec(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
+            maxbits = max(maxbits, abs_max(u, valid));
+        } else {
+            const f4 xn = model4(xv, sign4(u), st.c.decay ? gs.lam : 0.0f, gs);
+            store_vec(xn, xp, valid);
+            if (KIND == 1) {
+                for (int i = 0; i < gs.n; ++i)
+                    store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q,
+                              valid);
             }
         }
     }
-    if (KIND == 2) store_piece_max(maxbits, wave_max, piece_max + pc.wi);
+    if constexpr (KIND == 2 && !PIECE) {
+        if (w0 == 0) {
+            maxbits = wave_max(maxbits);
+            if (q == 0) atomicMax(piece_max + st.piece, maxbits);
+        }
+    }
+    if constexpr (PIECE) {
+        uint32_t* const strip_max = reinterpret_cast<uint32_t*>(x_end);
+        maxbits = wave_max(maxbits);
+        __syncthreads();  // the step-H values have been read
+        if (w0 == 0 && q == 0) strip_max[k] = maxbits;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int j = 1; j < kQuadWaves; ++j) maxbits = max(maxbits, strip_max[j]);
+            piece_max[quad_word(st, rows)] = maxbits;
+        }
+    }
+}
+
+// Zeroes the bound words that atomic maxima will raise.
+__global__ __launch_bounds__(kBlockThreads) void k_clear_words(uint4* __restrict__ words,
+                                                              int64_t n4) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlockThreads + threadIdx.x;
+    if (i < n4) words[i] = uint4{0, 0, 0, 0};
 }
 
 // ---------------------------------------------------------------- sync / init
@@ -886,6 +941,58 @@ dim3 local_grid(int64_t n_chunks, int n_workers, int map) {
     return chunk_grid(n_chunks, n_workers);
 }
 
+// Launch shape.  All kernels are bound by HBM, and what decides how much of
+// it they get is how many DRAM rows their reads and writes fight over.  Three
+// things keep that number down:
+// * Strips of 1 KiB per stream in grid order: the hardware deals consecutive
+//   work-groups to the 8 XCDs in turn, so all XCDs sweep the same few MB of
+//   every stream instead of eight regions far apart, and a row is used up
+//   while it is open.
+// * Few waves per CU: just enough requests in flight (about 48 KiB of reads
+//   per CU) to cover the latency.  Dynamic LDS that nothing uses holds the
+//   number of resident work-groups down.
+// * One wave per work-group where the kernel allows it, so a finished strip
+//   is replaced at once.
+// Local AdamW, GPT-2 small, n = 4, contiguous (% of 8 TB/s): 4 KiB pieces, an
+// eighth of the arena per XCD, all waves resident 70.6-73.1; 4 KiB pieces in
+// grid order, 12 waves per CU 79.8; 1 KiB strips 76.9 with all waves resident,
+// 79.4 with 16 per CU, 82.7 with 12, below 77 with 8.  State-blocked, n = 8:
+// 75.8 before, 84.6 now.
+//
+// Dynamic LDS that lets at most `groups` work-groups live on a CU (its 160 KiB
+// come in steps of 1280 bytes).
+constexpr unsigned lds_for(int groups) {
+    return groups >= kAllWaves ? 0u : static_cast<unsigned>(160 * 1024 / groups / 1280 * 1280);
+}
+// The same for work-groups of `waves` waves, at most `per_cu` waves per CU.
+constexpr unsigned lds_for(int per_cu, int waves) { return lds_for((per_cu + waves / 2) / waves); }
+
+// A launch that touches less than half the 256 MB last-level cache is over
+// before its rows fight: it is bound by latency, and takes all the waves that
+// fit (a local step's working set of 67 MB: round 83.4 us against 85.5 us).
+constexpr int64_t kSmallBytes = int64_t(128) << 20;
+
+// Strip groups of a launch, and the Rows its kernel finds them by.
+int64_t groups_of(int64_t n_chunks, const RepLayout& rl) {
+    return rl.groups > 0 ? rl.groups : n_chunks * (kStrips / kGroupStrips);
+}
+Rows rows_of(int64_t n_chunks, const RepLayout& rl, int map) {
+    return Rows{map, rl.groups > 0 ? static_cast<uint32_t>(n_chunks) : 0u};
+}
+dim3 strip_grid(int64_t n_chunks, const RepLayout& rl) {
+    return dim3(static_cast<unsigned>(groups_of(n_chunks, rl) * kGroupStrips));
+}
+dim3 quad_grid(int64_t n_chunks, const RepLayout& rl) {
+    return dim3(static_cast<unsigned>(groups_of(n_chunks, rl) * kGroupPieces));
+}
+// Whether a launch over `streams` arenas is small.
+bool small_launch(int64_t n_chunks, const RepLayout& rl, int streams) {
+    return groups_of(n_chunks, rl) * streams * (4 * kGroupElems) <= kSmallBytes;
+}
+int waves_for(int64_t n_chunks, const RepLayout& rl, int streams, int waves) {
+    return small_launch(n_chunks, rl, streams) ? kAllWaves : waves;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
@@ -922,33 +1029,70 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
     return hipGetLastError();
 }
 
+// Work-groups of the round end per CU, by waves per work-group.  Many waves
+// of a group wait for its last, so more waves are resident than in a local
+// step, and fewer groups the larger they are (swept 2 to 24 at GPT-2 small to
+// xl; with one worker 77.4% with 10-12, 72% with 8, 74% with 14).
+constexpr int round_end_groups(int waves) {
+    return waves == 1 ? 12 : waves == 2 ? 8 : waves == 3 ? 6 : waves == 4 ? 5 : 4;
+}
+
+// From here on the randomized round end clears the bound words and raises them
+// by atomic maxima, one strip per work-group; below, a work-group takes all
+// four strips of a word.  The four strips are slower (SGD, n = 16, 30M
+// parameters: 66% of 8 TB/s against 82%; AdamW, n = 4, 124M: 72% against 77%),
+// but the clearing is a launch of its own, ~4 us (3M parameters, n = 2: round
+// 81.6 us against 83.7 us).  In strip groups times workers, 134M elements.
+constexpr int64_t kAtomicBoundGroups = 65536;
+
+template <int BASE, int KIND, bool PIECE>
+static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const RoundEndArgs& a,
+                                   hipStream_t st) {
+    constexpr int strips = PIECE ? kQuadWaves : 1;
+    const dim3 grid = PIECE ? quad_grid(n_chunks, a.rl) : strip_grid(n_chunks, a.rl);
+    int workers = a.gs.n < kMaxRoundEndWaves / strips ? a.gs.n : kMaxRoundEndWaves / strips;
+    // A grid dimension holds fewer than 2^32 threads.
+    while (static_cast<int64_t>(grid.x) * workers * strips * kWave >= (int64_t(1) << 32))
+        workers /= 2;
+    const int groups = PIECE ? kAllWaves
+                             : waves_for(n_chunks, a.rl, 4 * a.gs.n + 2,
+                                         round_end_groups(workers) + (KIND == 2 ? 1 : 0));
+    const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
+    const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
+    hipLaunchKernelGGL((k_round_end<BASE, KIND, PIECE>), grid, dim3(workers * strips * kWave), lds,
+                       st, chunks, rows_of(n_chunks, a.rl, a.map), a.x, a.m, a.x_rep, a.rl, a.x_src,
+                       a.sl, a.g_rep, a.s1, a.s2, a.u, a.bound.piece_max, a.ml, workers, a.as, a.ss,
+                       a.gs);
+}
+
 template <int BASE, int KIND>
-static void launch_round_end_n(const Chunk* chunks, int64_t n_chunks, const RoundEndArgs& a,
-                               hipStream_t st) {
-    const dim3 grid = chunk_grid(n_chunks, 1), block(kBlockThreads);
-#define DSM_ROUND_END(NW)                                                                        \
-    hipLaunchKernelGGL((k_round_end<NW, BASE, KIND>), grid, block, 0, st, chunks, a.map, a.x, a.m,\
-                       a.x_rep, a.rl, a.x_src, a.sl, a.g_rep, a.s1, a.s2, a.u, a.bound.piece_max, \
-                       a.ml, a.as, a.ss, a.gs)
-    switch (a.gs.n) {
-        case 1: DSM_ROUND_END(1); break;
-        case 2: DSM_ROUND_END(2); break;
-        case 4: DSM_ROUND_END(4); break;
-        case 8: DSM_ROUND_END(8); break;
-        default: DSM_ROUND_END(0); break;
+static void launch_round_end_kind(const Chunk* chunks, int64_t n_chunks, const RoundEndArgs& a,
+                                  hipStream_t st) {
+    if constexpr (KIND == 2) {
+        // A word's four strips keep 4 n KiB of step-H values in LDS.
+        if (a.gs.n <= kMaxRoundEndWaves &&
+            groups_of(n_chunks, a.rl) * a.gs.n < kAtomicBoundGroups) {
+            launch_round_end_shape<BASE, KIND, true>(chunks, n_chunks, a, st);
+            return;
+        }
+        const int64_t n4 = n_chunks * kSplit / 4;
+        hipLaunchKernelGGL(k_clear_words,
+                           dim3(static_cast<unsigned>((n4 + kBlockThreads - 1) / kBlockThreads)),
+                           dim3(kBlockThreads), 0, st,
+                           reinterpret_cast<uint4*>(a.bound.piece_max), n4);
     }
-#undef DSM_ROUND_END
+    launch_round_end_shape<BASE, KIND, false>(chunks, n_chunks, a, st);
 }
 
 template <int BASE>
 static void launch_round_end_base(const Chunk* chunks, int64_t n_chunks, const RoundEndArgs& a,
                                   int kind, hipStream_t st) {
     if (kind == 0)
-        launch_round_end_n<BASE, 0>(chunks, n_chunks, a, st);
+        launch_round_end_kind<BASE, 0>(chunks, n_chunks, a, st);
     else if (kind == 1)
-        launch_round_end_n<BASE, 1>(chunks, n_chunks, a, st);
+        launch_round_end_kind<BASE, 1>(chunks, n_chunks, a, st);
     else
-        launch_round_end_n<BASE, 2>(chunks, n_chunks, a, st);
+        launch_round_end_kind<BASE, 2>(chunks, n_chunks, a, st);
 }
 
 template <int BASE>
@@ -987,9 +1131,11 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
 
 // Level two of the tensor bound, after a first pass has stored its piece
 // maxima.  Also run with no chunks at all, so that every bound is written.
-static void launch_bound_reduce(const BoundWords& bw, int n_tensors, hipStream_t st) {
+static void launch_bound_reduce(const Chunk* chunks, const BoundWords& bw, int n_tensors,
+                                bool sparse, hipStream_t st) {
     hipLaunchKernelGGL(k_bound_reduce, dim3(static_cast<unsigned>(n_tensors)),
-                       dim3(kReduceThreads), 0, st, bw.piece_max, bw.chunk0, bw.bits);
+                       dim3(kReduceThreads), 0, st, chunks, bw.piece_max, bw.chunk0, bw.bits,
+                       sparse);
 }
 
 static void launch_rand_pass2(const Chunk* chunks, int64_t n_chunks, float* x, float* x_rep,
@@ -1016,7 +1162,8 @@ hipError_t launch_round_end(const Chunk* chunks, int64_t n_chunks, int n_tensors
         else
             launch_round_end_base<kBaseSgd>(chunks, n_chunks, a, kind, st);
     }
-    if (randomized && n_tensors > 0) launch_bound_reduce(a.bound, n_tensors, st);
+    if (randomized && n_tensors > 0)
+        launch_bound_reduce(chunks, a.bound, n_tensors, a.rl.groups > 0, st);
     if (randomized && n_chunks > 0)
         launch_rand_pass2(chunks, n_chunks, a.x, a.x_rep, a.rl, a.u, a.bound.bits, a.gs,
                           broadcast, a.map_pass2, st);
@@ -1094,7 +1241,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
         }
 #undef DSM_PASS1
     }
-    if (n_tensors > 0) launch_bound_reduce(bw, n_tensors, st);
+    if (n_tensors > 0) launch_bound_reduce(chunks, bw, n_tensors, rl.groups > 0, st);
     if (n_chunks > 0)
         launch_rand_pass2(chunks, n_chunks, x, x_rep, rl, u, bw.bits, sc, broadcast, map, st);
     return hipGetLastError();

@@ -75,6 +75,7 @@ struct Layout {
     std::vector<int64_t> offsets;
     int64_t arena_elems = 0;
     int64_t n_chunks = 0;
+    int64_t groups = 0;  // strip groups of the chunks that hold elements
     int64_t chunk_bytes = 0;
     int64_t bounds_off = 0;
     int64_t chunk0_off = 0;
@@ -159,6 +160,8 @@ dsm_status make_layout(const dsm_problem* p, Layout* L, std::vector<dsm::Chunk>*
                 c.len = static_cast<int32_t>(std::min<int64_t>(dsm::kChunkElems, p->numel[i] - j));
                 c.tensor = static_cast<uint32_t>(i);
                 c.decay = dec;
+                c.group0 = static_cast<uint32_t>(L->groups);
+                L->groups += (c.len + dsm::kGroupElems - 1) / dsm::kGroupElems;
                 chunks->push_back(c);
             }
         }
@@ -421,6 +424,7 @@ dsm_status init_context(const dsm_problem* problem, const dsm_buffers* caller, d
                         adamw ? " and s2_rep" : "", static_cast<long long>(gap),
                         static_cast<long long>(2 * gap), adamw ? " and 3x that" : "", nb);
     }
+    if (dsm::sparse_chunks(L.groups, L.n_chunks)) rep.groups = static_cast<int32_t>(L.groups);
     if (L.workspace_bytes > 0) {
         if (!b->workspace) return fail(nullptr, DSM_ERR_INVALID_ARG, "workspace is NULL");
         if (!aligned256(b->workspace))
@@ -688,19 +692,12 @@ dsm_status dsm_test_philox(uint64_t seed, uint32_t tensor, int64_t t, int64_t q0
     return DSM_OK;
 }
 
-#if DSM_UNROLL == 1 && DSM_ITERS == 1 && DSM_BLOCK_THREADS == 256
-static_assert(dsm::kPieceElems == DSM_PIECE_ELEMS, "dsm.h's piece size is the default build's");
-#endif
+static_assert(dsm::kPieceElems == DSM_PIECE_ELEMS, "dsm.h promises the piece size");
 
 dsm_status dsm_test_stream(int32_t kind, float* dev_buf, int64_t n_elems, uint32_t* dev_words,
                            uint32_t pattern, void* stream) {
     if (kind != DSM_STREAM_READ && kind != DSM_STREAM_WRITE)
         return fail(nullptr, DSM_ERR_INVALID_ARG, "kind must be DSM_STREAM_READ or DSM_STREAM_WRITE");
-    // A build with other work-group shape knobs has another piece size than
-    // the one dsm.h promises for the word array.
-    if (dsm::kPieceElems != DSM_PIECE_ELEMS)
-        return fail(nullptr, DSM_ERR_UNSUPPORTED, "this build's piece is %lld elements, not %d",
-                    static_cast<long long>(dsm::kPieceElems), DSM_PIECE_ELEMS);
     if (n_elems < 0 || n_elems % dsm::kPieceElems != 0)
         return fail(nullptr, DSM_ERR_INVALID_ARG, "n_elems must be a non-negative multiple of %lld",
                     static_cast<long long>(dsm::kPieceElems));
