@@ -142,7 +142,7 @@ struct GlobalScalars {
 // index itself (XCD k takes piece k mod 8 of every chunk); 1, XCD k takes the
 // k-th eighth of the grid row, in order; 2, XCD k takes whole chunks.  The
 // best map of each kernel kind depends on the replica layout (measured), so
-// the runtime keeps one set per layout; the fused round end go over strips instead, and take 0.
+// the runtime keeps one set per layout; the fused round end and the local steps go over strips instead, and take 0.
 // global: the global steps and the randomized second pass of the round end;
 // copy: the broadcast of dsm_sync and the initial copy of dsm_init.
 //
@@ -155,7 +155,8 @@ constexpr int kQuads = 8;  // work-groups of four waves
 struct XcdMaps {
     int local, round_end, from_x, global, copy;
 };
-constexpr XcdMaps kMapsByLayout[3] = {{1, 0, 2, 0, 0}, {1, 0, 1, 0, 1}, {1 + kInterleaveWorkers, 0, 1, 1, 1}};
+constexpr XcdMaps kMapsByLayout[3] = {{0, 0, kInterleaveWorkers, 0, 0}, {0, 0, kInterleaveWorkers, 0, 1},
+                                      {kInterleaveWorkers, 0, kInterleaveWorkers, 1, 1}};
 
 // How a kernel finds its strips: the launch map, and the number of chunks when
 // it goes over the strip groups that hold elements (RepLayout::groups), else 0.

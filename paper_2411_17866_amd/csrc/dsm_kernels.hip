@@ -122,21 +122,6 @@ __device__ __forceinline__ Piece piece_of(const Chunk* __restrict__ chunks, int 
     return piece_at(chunks, work_index(map & 3));
 }
 
-// The piece and worker of a local-step work-group.  Without kInterleaveWorkers
-// in the map the grid is (pieces, workers) and runs worker by worker; with it
-// the grid is one row of pieces x workers, worker fastest, so consecutive
-// work-groups take the same piece of successive workers.
-__device__ __forceinline__ Piece local_piece(const Chunk* __restrict__ chunks, int map, int worker0,
-                                             int n_workers, int64_t& w) {
-    if (map & kInterleaveWorkers) {
-        const uint32_t f = work_index(map & 3);
-        w = worker0 + static_cast<int64_t>(f % static_cast<uint32_t>(n_workers));
-        return piece_at(chunks, f / static_cast<uint32_t>(n_workers));
-    }
-    w = worker0 + static_cast<int64_t>(blockIdx.y);
-    return piece_at(chunks, work_index(map & 3));
-}
-
 // ---------------------------------------------------------------- strips
 
 // A strip of a chunk: 64 consecutive float4 groups, one per lane of a wave
@@ -215,6 +200,22 @@ __device__ __forceinline__ uint32_t quad_word(const Strip& st, const Rows& rows)
     return rows.sparse_chunks > 0 ? st.piece : blockIdx.x;
 }
 
+// The strip and worker of a local-step work-group.  Without kInterleaveWorkers
+// in the map the grid is (strips, workers) and runs worker by worker; with it
+// the grid is one row of strips x workers in which the eight strips of a
+// group, one per XCD, of one worker are followed by those of the next worker.
+__device__ __forceinline__ Strip local_strip(const Chunk* __restrict__ chunks, const Rows& rows,
+                                             int worker0, int n_workers, int64_t& w) {
+    const uint32_t b = blockIdx.x;
+    if (rows.map & kInterleaveWorkers) {
+        const uint32_t g = b / kGroupStrips, n = static_cast<uint32_t>(n_workers);
+        w = worker0 + static_cast<int64_t>(g % n);
+        return strip_at(chunks, rows, (g / n) * kGroupStrips + b % kGroupStrips);
+    }
+    w = worker0 + static_cast<int64_t>(blockIdx.y);
+    return strip_at(chunks, rows, b);
+}
+
 // ---------------------------------------------------------------- AdamW
 
 // Correctly rounded square root (the build asks for correctly rounded fp32
@@ -242,49 +243,45 @@ __device__ __forceinline__ void adamw4(f4& x, f4 g, f4& m, f4& v, float lam, con
     x = x - st;
 }
 
+// Loads a group of a local step's starting point.  SHARED: the n workers of
+// the launch all start from the global model, in the interleaved order, so
+// the line is wanted by n waves of this XCD at about the same time: a plain
+// load keeps it in the XCD's L2 for the others and x comes from HBM once.
+template <bool SHARED>
+__device__ __forceinline__ f4 load_start(const f4* p) {
+    if constexpr (SHARED)
+        return *p;
+    else
+        return ntload(p);
+}
+
 // Worker w reads its step's starting point at x_src + rep_index(sl, w, e)
 // (its own replica, or with a zero copy stride the global model x when the
 // replicas are stale after a global step without broadcast) and writes the
 // result to its replica, x_rep + rep_index(rl, w, e); its gradient and
 // moments sit at rep_index(ml.g / ml.s1 / ml.s2, w, e) of their buffers.  The two may be the
-// same memory, so neither pointer is __restrict__; each thread loads every
+// same memory, so neither pointer is __restrict__; each lane loads every
 // stream of its group before it stores.
-__global__ __launch_bounds__(kBlockThreads) void k_local_adamw(
-    const Chunk* __restrict__ chunks, int map, float* x_rep, RepLayout rl, const float* x_src,
+template <bool SHARED>
+__global__ __launch_bounds__(kWave) void k_local_adamw(
+    const Chunk* __restrict__ chunks, Rows rows, float* x_rep, RepLayout rl, const float* x_src,
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1,
     float* __restrict__ s2, StateLayout ml, int worker0, int n_workers, AdamScalars sc) {
     int64_t w;
-    const Piece pc = local_piece(chunks, map, worker0, n_workers, w);
-    f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, pc.e0));
-    const f4* xs = reinterpret_cast<const f4*>(x_src + rep_index(sl, w, pc.e0));
-    const f4* __restrict__ gp = reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, pc.e0));
-    f4* __restrict__ mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, pc.e0));
-    f4* __restrict__ vp = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, w, pc.e0));
-    const float lam = pc.c.decay ? sc.wd : 0.0f;
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], gv[kUnroll], mv[kUnroll], vv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xs + q);
-                gv[k] = ntload(gp + q);
-                mv[k] = ntload(mp + q);
-                vv[k] = ntload(vp + q);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                const int valid = pc.valid0 - 4 * q;
-                adamw4(xv[k], gv[k], mv[k], vv[k], lam, sc);
-                store_vec(xv[k], xp + q, valid);
-                store_vec(mv[k], mp + q, valid);
-                store_vec(vv[k], vp + q, valid);
-            }
-        }
-    }
+    const Strip st = local_strip(chunks, rows, worker0, n_workers, w);
+    const int q = lane_id();
+    if (q >= st.nq) return;
+    f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
+    f4* mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, st.e0)) + q;
+    f4* vp = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, w, st.e0)) + q;
+    f4 x = load_start<SHARED>(reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
+    const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
+    f4 m = ntload(mp), v = ntload(vp);
+    adamw4(x, g, m, v, st.c.decay ? sc.wd : 0.0f, sc);
+    const int valid = st.valid0 - 4 * q;
+    store_vec(x, xp, valid);
+    store_vec(m, mp, valid);
+    store_vec(v, vp, valid);
 }
 
 // ---------------------------------------------------------------- SGD + momentum
@@ -297,38 +294,24 @@ __device__ __forceinline__ void sgdm4(f4& x, f4 g, f4& m, const SgdScalars& s) {
     x = x - st;
 }
 
-__global__ __launch_bounds__(kBlockThreads) void k_local_sgdm(
-    const Chunk* __restrict__ chunks, int map, float* x_rep, RepLayout rl, const float* x_src,
+template <bool SHARED>
+__global__ __launch_bounds__(kWave) void k_local_sgdm(
+    const Chunk* __restrict__ chunks, Rows rows, float* x_rep, RepLayout rl, const float* x_src,
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1, StateLayout ml,
     int worker0, int n_workers, SgdScalars sc) {
     int64_t w;
-    const Piece pc = local_piece(chunks, map, worker0, n_workers, w);
-    f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, pc.e0));
-    const f4* xs = reinterpret_cast<const f4*>(x_src + rep_index(sl, w, pc.e0));
-    const f4* __restrict__ gp = reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, pc.e0));
-    f4* __restrict__ mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, pc.e0));
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], gv[kUnroll], mv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xs + q);
-                gv[k] = ntload(gp + q);
-                mv[k] = ntload(mp + q);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                const int valid = pc.valid0 - 4 * q;
-                sgdm4(xv[k], gv[k], mv[k], sc);
-                store_vec(xv[k], xp + q, valid);
-                store_vec(mv[k], mp + q, valid);
-            }
-        }
-    }
+    const Strip st = local_strip(chunks, rows, worker0, n_workers, w);
+    const int q = lane_id();
+    if (q >= st.nq) return;
+    f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
+    f4* mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, st.e0)) + q;
+    f4 x = load_start<SHARED>(reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
+    const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
+    f4 m = ntload(mp);
+    sgdm4(x, g, m, sc);
+    const int valid = st.valid0 - 4 * q;
+    store_vec(x, xp, valid);
+    store_vec(m, mp, valid);
 }
 
 // ---------------------------------------------------------------- global step
@@ -670,70 +653,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
     }
 }
 
-// ---------------------------------------------------------------- local step from x
+// ---------------------------------------------------------------- fused round end
 
-// Base optimizer of the kernels that take local steps of several workers.
+// Base optimizer of the fused round end.
 constexpr int kBaseAdamW = 0;
 constexpr int kBaseSgd = 1;
-
-// Local step of every worker when every replica is stale (after a global
-// step without broadcast): each worker's x_{t+1,0} is the global model, so
-// the work-group reads x once and takes the step of all n workers on it,
-// writing each replica, instead of one pass per worker that re-reads x.  The
-// per-element arithmetic is adamw4 / sgdm4, as in the per-worker kernels.
-template <int N, int BASE>
-__global__ __launch_bounds__(kBlockThreads) void k_local_from_x(
-    const Chunk* __restrict__ chunks, int map, const float* __restrict__ x, float* __restrict__ x_rep,
-    RepLayout rl, const float* __restrict__ g_rep, float* __restrict__ s1,
-    float* __restrict__ s2, StateLayout ml, int n_rt, AdamScalars as, SgdScalars ss) {
-    const Piece pc = piece_of(chunks, map);
-    const int n = N > 0 ? N : n_rt;
-    const f4* __restrict__ xp = reinterpret_cast<const f4*>(x + pc.e0);
-    const float lam = pc.c.decay ? as.wd : 0.0f;
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) xv[k] = ntload(xp + q);
-        }
-#pragma unroll(N > 0 ? N : 1)
-        for (int i = 0; i < (N > 0 ? N : n); ++i) {
-            f4* __restrict__ xr = reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0));
-            const f4* __restrict__ gp = reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, pc.e0));
-            f4* __restrict__ s1p = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, pc.e0));
-            f4* __restrict__ s2p = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, pc.e0));
-            f4 gi[kUnroll], mi[kUnroll], vi[kUnroll];
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k) {
-                const int q = q0 + k * kBlockThreads;
-                if (q < pc.nq) {
-                    gi[k] = ntload(gp + q);
-                    mi[k] = ntload(s1p + q);
-                    if (BASE == kBaseAdamW) vi[k] = ntload(s2p + q);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k) {
-                const int q = q0 + k * kBlockThreads;
-                if (q < pc.nq) {
-                    const int valid = pc.valid0 - 4 * q;
-                    f4 xi = xv[k];
-                    if (BASE == kBaseAdamW) {
-                        adamw4(xi, gi[k], mi[k], vi[k], lam, as);
-                        store_vec(vi[k], s2p + q, valid);
-                    } else {
-                        sgdm4(xi, gi[k], mi[k], ss);
-                    }
-                    store_vec(xi, xr + q, valid);
-                    store_vec(mi[k], s1p + q, valid);
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- fused round end
 
 // The last local step of every worker (Algorithm 2 or 3, Eq. (4)) fused with
 // the global step (all-reduce, Eqs. (6)-(8)): each worker's step-H replica
@@ -933,14 +857,6 @@ dim3 chunk_grid(int64_t n_chunks, int n_workers) {
     return dim3(static_cast<unsigned>(n_chunks * kSplit), static_cast<unsigned>(n_workers), 1);
 }
 
-// Grid of a local step: one row of pieces x workers when the map interleaves
-// the workers, else (pieces, workers).
-dim3 local_grid(int64_t n_chunks, int n_workers, int map) {
-    if (map & kInterleaveWorkers)
-        return dim3(static_cast<unsigned>(n_chunks * kSplit * n_workers), 1, 1);
-    return chunk_grid(n_chunks, n_workers);
-}
-
 // Launch shape.  All kernels are bound by HBM, and what decides how much of
 // it they get is how many DRAM rows their reads and writes fight over.  Three
 // things keep that number down:
@@ -967,6 +883,13 @@ constexpr unsigned lds_for(int groups) {
 // The same for work-groups of `waves` waves, at most `per_cu` waves per CU.
 constexpr unsigned lds_for(int per_cu, int waves) { return lds_for((per_cu + waves / 2) / waves); }
 
+// Waves per CU by kernel, swept from 6 to 32 at GPT-2 small to xl.  Local
+// steps: AdamW (four loads) 12, SGD (three, and little arithmetic) 20: medium,
+// n = 8, 84.0% against 83.2% with 16 and 78% with 14.  From the shared x one
+// load of most waves hits the L2, so a few more.
+constexpr int kAdamWWaves = 12, kAdamWSharedWaves = 14;
+constexpr int kSgdWaves = 20, kSgdSharedWaves = 18;
+
 // A launch that touches less than half the 256 MB last-level cache is over
 // before its rows fight: it is bound by latency, and takes all the waves that
 // fit (a local step's working set of 67 MB: round 83.4 us against 85.5 us).
@@ -985,6 +908,14 @@ dim3 strip_grid(int64_t n_chunks, const RepLayout& rl) {
 dim3 quad_grid(int64_t n_chunks, const RepLayout& rl) {
     return dim3(static_cast<unsigned>(groups_of(n_chunks, rl) * kGroupPieces));
 }
+// Grid of a local step: one row of strips x workers when the map interleaves
+// the workers, else (strips, workers).
+dim3 local_grid(int64_t n_chunks, const RepLayout& rl, int n_workers, int map) {
+    const unsigned n = static_cast<unsigned>(n_workers);
+    const dim3 row = strip_grid(n_chunks, rl);
+    return map & kInterleaveWorkers ? dim3(row.x * n) : dim3(row.x, n);
+}
+
 // Whether a launch over `streams` arenas is small.
 bool small_launch(int64_t n_chunks, const RepLayout& rl, int streams) {
     return groups_of(n_chunks, rl) * streams * (4 * kGroupElems) <= kSmallBytes;
@@ -1012,9 +943,10 @@ hipError_t launch_local_adamw(const Chunk* chunks, int64_t n_chunks, float* x_re
                               const AdamScalars& sc, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    hipLaunchKernelGGL(k_local_adamw, local_grid(n_chunks, n_workers, map), dim3(kBlockThreads), 0,
-                       st, chunks, map, x_rep, rl, x_src, sl, g_rep, s1, s2, ml, worker0, n_workers,
-                       sc);
+    const int waves = waves_for(n_chunks, rl, 4 * n_workers, kAdamWWaves);
+    hipLaunchKernelGGL(k_local_adamw<false>, local_grid(n_chunks, rl, n_workers, map), dim3(kWave),
+                       lds_for(waves), st, chunks, rows_of(n_chunks, rl, map), x_rep, rl, x_src, sl,
+                       g_rep, s1, s2, ml, worker0, n_workers, sc);
     return hipGetLastError();
 }
 
@@ -1024,8 +956,37 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
                              int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    hipLaunchKernelGGL(k_local_sgdm, local_grid(n_chunks, n_workers, map), dim3(kBlockThreads), 0,
-                       st, chunks, map, x_rep, rl, x_src, sl, g_rep, s1, ml, worker0, n_workers, sc);
+    const int waves = waves_for(n_chunks, rl, 3 * n_workers, kSgdWaves);
+    hipLaunchKernelGGL(k_local_sgdm<false>, local_grid(n_chunks, rl, n_workers, map), dim3(kWave),
+                       lds_for(waves), st, chunks, rows_of(n_chunks, rl, map), x_rep, rl, x_src, sl,
+                       g_rep, s1, ml, worker0, n_workers, sc);
+    return hipGetLastError();
+}
+
+// Local step of every worker when every replica is stale (after a global step
+// without broadcast): each worker starts from the global model.  The workers
+// are interleaved, so that x is read from HBM once for all of them (and per
+// worker in the rare launch whose row is too long to interleave).  One wave
+// taking all n steps of a strip, with its 3 n + 1 streams at a time, ran at
+// 66.1% (small, n = 8, state-blocked) and 67.5% (n = 4, contiguous) of 8 TB/s
+// over the same bytes; this at 83.1% and 78.3%.
+hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const float* x,
+                               float* x_rep, RepLayout rl, const float* g_rep, float* s1,
+                               float* s2, StateLayout ml, int n, bool adamw,
+                               const AdamScalars& as, const SgdScalars& ss, int map,
+                               hipStream_t st) {
+    if (n_chunks == 0) return hipSuccess;
+    map = local_map(n_chunks, n, map);
+    const dim3 grid = local_grid(n_chunks, rl, n, map), block(kWave);
+    const Rows rows = rows_of(n_chunks, rl, map);
+    const int waves = adamw ? waves_for(n_chunks, rl, 4 * n, kAdamWSharedWaves)
+                            : waves_for(n_chunks, rl, 3 * n, kSgdSharedWaves);
+    if (adamw)
+        hipLaunchKernelGGL(k_local_adamw<true>, grid, block, lds_for(waves), st, chunks, rows,
+                           x_rep, rl, x, single_copy(), g_rep, s1, s2, ml, 0, n, as);
+    else
+        hipLaunchKernelGGL(k_local_sgdm<true>, grid, block, lds_for(waves), st, chunks, rows, x_rep,
+                           rl, x, single_copy(), g_rep, s1, ml, 0, n, ss);
     return hipGetLastError();
 }
 
@@ -1093,40 +1054,6 @@ static void launch_round_end_base(const Chunk* chunks, int64_t n_chunks, const R
         launch_round_end_kind<BASE, 1>(chunks, n_chunks, a, st);
     else
         launch_round_end_kind<BASE, 2>(chunks, n_chunks, a, st);
-}
-
-template <int BASE>
-static void launch_local_from_x_n(const Chunk* chunks, int64_t n_chunks, const float* x,
-                                  float* x_rep, RepLayout rl, const float* g_rep, float* s1,
-                                  float* s2, StateLayout ml, int n, const AdamScalars& as,
-                                  const SgdScalars& ss, int map, hipStream_t st) {
-    const dim3 grid = chunk_grid(n_chunks, 1), block(kBlockThreads);
-#define DSM_LOCAL_FROM_X(NW)                                                                   \
-    hipLaunchKernelGGL((k_local_from_x<NW, BASE>), grid, block, 0, st, chunks, map, x, x_rep, rl,\
-                       g_rep, s1, s2, ml, n, as, ss)
-    switch (n) {
-        case 1: DSM_LOCAL_FROM_X(1); break;
-        case 2: DSM_LOCAL_FROM_X(2); break;
-        case 4: DSM_LOCAL_FROM_X(4); break;
-        case 8: DSM_LOCAL_FROM_X(8); break;
-        default: DSM_LOCAL_FROM_X(0); break;
-    }
-#undef DSM_LOCAL_FROM_X
-}
-
-hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const float* x,
-                               float* x_rep, RepLayout rl, const float* g_rep, float* s1,
-                               float* s2, StateLayout ml, int n, bool adamw,
-                               const AdamScalars& as, const SgdScalars& ss, int map,
-                               hipStream_t st) {
-    if (n_chunks == 0) return hipSuccess;
-    if (adamw)
-        launch_local_from_x_n<kBaseAdamW>(chunks, n_chunks, x, x_rep, rl, g_rep, s1, s2, ml, n,
-                                          as, ss, map, st);
-    else
-        launch_local_from_x_n<kBaseSgd>(chunks, n_chunks, x, x_rep, rl, g_rep, s1, s2, ml, n, as,
-                                        ss, map, st);
-    return hipGetLastError();
 }
 
 // Level two of the tensor bound, after a first pass has stored its piece
