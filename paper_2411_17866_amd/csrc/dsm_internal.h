@@ -25,8 +25,7 @@ static_assert(kChunkElems % kGroupElems == 0, "a chunk must split into whole str
 // each with one word of the randomized sign's bound.
 constexpr int kQuadWaves = 4;
 constexpr int kBlockThreads = kQuadWaves * kWave;
-constexpr int kUnroll = 1;  // float4 groups per stream of a thread of a piece
-constexpr int kPieceVec = kBlockThreads * kUnroll;
+constexpr int kPieceVec = kBlockThreads;
 constexpr int kSplit = kChunkElems / 4 / kPieceVec;  // pieces per chunk
 constexpr int kGroupPieces = kGroupStrips / kQuadWaves;
 static_assert(kSplit % kXcds == 0, "the strips of a quad must lie in one chunk");
@@ -138,25 +137,31 @@ struct GlobalScalars {
     float eta, eps;
 };
 
-// How a launch's work-group index maps to its piece (the XCD map): 0, the
-// index itself (XCD k takes piece k mod 8 of every chunk); 1, XCD k takes the
-// k-th eighth of the grid row, in order; 2, XCD k takes whole chunks.  The
-// best map of each kernel kind depends on the replica layout (measured), so
-// the runtime keeps one set per layout; the fused round end and the local steps go over strips instead, and take 0.
+// How a launch goes over the strips, by kernel kind and replica layout.
+// Without flags, one-wave work-groups take the strips in order.
+//
+// kInterleaveWorkers (local steps): the grid is one row of strips x workers in
+// which a strip group of one worker is followed by the same group of the next.
+// With the state blocked, consecutive work-groups then sweep whole blocks (xl,
+// n = 4: 85.4% of 8 TB/s; a strip instead of a group at a time 83.2%).  For the
+// step from x (from_x), in every layout, it also brings the n reads of an x
+// line together.
+//
+// kQuads (the other kinds): work-groups of four waves.  Ahead where a kernel
+// writes every replica from blocks (global step, state-blocked, n = 8: 79.2%
+// against 78.4%; sync 82-88% in all layouts, 79-81% with one wave), behind
+// elsewhere (global step, contiguous, n = 4: 78.0% against 78.7%).
 // global: the global steps and the randomized second pass of the round end;
 // copy: the broadcast of dsm_sync and the initial copy of dsm_init.
-//
-// A local step's map may add kInterleaveWorkers: its grid is then one row of
-// pieces x workers, worker fastest, so consecutive work-groups take the same
-// piece of successive workers (with the state blocked, one block at a time)
-// instead of running worker by worker.
 constexpr int kInterleaveWorkers = 4;
-constexpr int kQuads = 8;  // work-groups of four waves
+constexpr int kQuads = 8;
 struct XcdMaps {
     int local, round_end, from_x, global, copy;
 };
-constexpr XcdMaps kMapsByLayout[3] = {{0, 0, kInterleaveWorkers, 0, 0}, {0, 0, kInterleaveWorkers, 0, 1},
-                                      {kInterleaveWorkers, 0, kInterleaveWorkers, 1, 1}};
+constexpr XcdMaps kMapsByLayout[3] = {
+    {0, 0, kInterleaveWorkers, 0, kQuads},                        // contiguous
+    {0, 0, kInterleaveWorkers, 0, kQuads},                        // blocked
+    {kInterleaveWorkers, 0, kInterleaveWorkers, kQuads, kQuads}}; // state-blocked
 
 // How a kernel finds its strips: the launch map, and the number of chunks when
 // it goes over the strip groups that hold elements (RepLayout::groups), else 0.

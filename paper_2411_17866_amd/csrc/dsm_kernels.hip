@@ -1,12 +1,13 @@
 // gfx950 kernels of distributed sign momentum with local steps
 // (arXiv 2411.17866, Algorithm 1).
 //
-// Every kernel streams fp32 arenas: each work-group takes one piece of one
-// chunk of one tensor (Chunk; by default 256 threads x one float4 = 1024
-// elements), each thread moves 128-bit (float4) groups with nontemporal loads
-// and stores, consecutive threads touch consecutive 16-byte groups, and every
-// element is read and written once per pass.  Nothing here is a
-// dense contraction, so there is no MFMA; the bound is HBM bandwidth.
+// Every kernel streams fp32 arenas: a wave takes one strip (64 lanes x one
+// float4 = 256 elements, 1 KiB per stream) of one chunk of one tensor, with
+// 128-bit nontemporal loads and stores, consecutive lanes on consecutive
+// 16-byte groups, and every element is read and written once per pass.
+// Nothing here is a dense contraction, so there is no MFMA; the bound is HBM
+// bandwidth, and what is left to gain is how close the mix of read and write
+// streams comes to it (see "Launch shape" below).
 //
 // Arithmetic: fp32, one IEEE round-to-nearest operation per written
 // operation, in the order the formulas are written; no contraction into FMA
@@ -54,72 +55,11 @@ __device__ __forceinline__ void store_vec(f4 v, f4* p, int valid) {
 // Contiguous copies use shift 62 (the block term vanishes) and copy_stride =
 // d_pad; 64 KiB blocks interleaved by copy use shift 14, block_stride =
 // n * 16384 and copy_stride = 16384; "every copy is x" uses shift 62 and
-// copy_stride 0.  A piece never crosses a block, so one base per piece and
-// copy serves every thread of the work-group.
+// copy_stride 0.  A strip never crosses a block, so one base per strip and
+// copy serves the whole wave.
 __device__ __forceinline__ int64_t rep_index(const RepLayout& L, int64_t i, int64_t e) {
     const int64_t mask = (int64_t(1) << L.shift) - 1;
     return (e >> L.shift) * L.block_stride + i * L.copy_stride + (e & mask);
-}
-
-// The piece of a chunk this work-group processes: work item w (below) takes
-// piece w % kSplit of chunk w / kSplit, kPieceVec float4 groups from group
-// (w % kSplit) * kPieceVec of the chunk on (fewer at the chunk's end).
-// Work-groups are short-lived and handle one piece each, so the addresses in
-// flight form compact fronts that sweep the arena.
-struct Piece {
-    Chunk c;
-    uint32_t wi;     // piece index: chunk wi / kSplit, piece wi % kSplit of it
-    int nq;          // float4 groups in the piece (0 past the chunk's end)
-    int valid0;      // lanes of the chunk from the piece's first group on
-    int64_t e0;      // arena element of the piece's first group
-    uint32_t j4;     // in-tensor index of the first group, divided by 4
-};
-
-// Work item of this work-group.  MAP 0: the work-group index itself (XCD k
-// takes piece k mod 8 of every chunk).  1: XCD k takes the k-th eighth of the
-// grid row, in order.  2: XCD k takes whole chunks (chunk 8r + k in group r).
-// Modes 1 and 2 are bijections on a prefix of the row and the identity on the
-// rest.
-template <int MAP>
-__device__ __forceinline__ uint32_t work_index() {
-    const uint32_t b = blockIdx.x;
-    if constexpr (MAP == 1) {
-        const uint32_t per = gridDim.x / kXcds;
-        if (b >= per * kXcds) return b;
-        return (b % kXcds) * per + b / kXcds;
-    } else if constexpr (MAP == 2) {
-        const uint32_t group = kXcds * kSplit;
-        if (b >= (gridDim.x / group) * group) return b;
-        const uint32_t r = b / kXcds, x = b % kXcds;
-        return (r / kSplit) * group + x * kSplit + r % kSplit;
-    } else {
-        return b;
-    }
-}
-
-// The map is a launch argument (the runtime picks it per kernel kind and
-// replica layout) and uniform over the grid, so the branch is scalar.
-__device__ __forceinline__ uint32_t work_index(int map) {
-    if (map == 1) return work_index<1>();
-    if (map == 2) return work_index<2>();
-    return work_index<0>();
-}
-
-__device__ __forceinline__ Piece piece_at(const Chunk* __restrict__ chunks, uint32_t wi) {
-    Piece pc;
-    pc.wi = wi;
-    pc.c = chunks[wi / kSplit];
-    const int nvec = (pc.c.len + 3) >> 2;
-    const int q_lo = static_cast<int>(wi % kSplit) * kPieceVec;
-    pc.nq = max(0, min(nvec, q_lo + kPieceVec) - q_lo);
-    pc.valid0 = pc.c.len - 4 * q_lo;
-    pc.e0 = pc.c.off + 4 * static_cast<int64_t>(q_lo);
-    pc.j4 = static_cast<uint32_t>(pc.c.j0 >> 2) + static_cast<uint32_t>(q_lo);
-    return pc;
-}
-
-__device__ __forceinline__ Piece piece_of(const Chunk* __restrict__ chunks, int map) {
-    return piece_at(chunks, work_index(map & 3));
 }
 
 // ---------------------------------------------------------------- strips
@@ -321,10 +261,12 @@ __device__ __forceinline__ float sign_of(float u) {
     return u > 0.0f ? 1.0f : (u < 0.0f ? -1.0f : (u == u ? 0.0f : u));
 }
 
-// Worker sum of (x - x_i) over the n replicas of group q of the piece that
+// Worker sum of (x - x_i) over the n replicas of group q of the strip that
 // starts at arena element e0, in worker order, divided by n.  N > 0:
 // compile-time worker count (a power of two, so the division is the exact
-// multiplication by 1/n); N == 0: runtime count.
+// multiplication by 1/n), every replica's load in flight together; N == 0:
+// runtime count, kReplicaBatch loads in flight at a time.
+constexpr int kReplicaBatch = 4;
 template <int N>
 __device__ __forceinline__ f4 worker_mean_diff(f4 xv, const float* __restrict__ x_rep,
                                                const RepLayout& rl, int64_t e0, int q,
@@ -339,9 +281,20 @@ __device__ __forceinline__ f4 worker_mean_diff(f4 xv, const float* __restrict__ 
         for (int i = 1; i < N; ++i) acc = acc + (xv - r[i]);
         return acc * s.inv_n;
     } else {
-        f4 acc = xv - ntload(reinterpret_cast<const f4*>(x_rep + rep_index(rl, 0, e0)) + q);
-        for (int i = 1; i < s.n; ++i)
-            acc = acc + (xv - ntload(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i, e0)) + q));
+        f4 acc;
+        for (int i0 = 0; i0 < s.n; i0 += kReplicaBatch) {
+            f4 r[kReplicaBatch];
+#pragma unroll
+            for (int k = 0; k < kReplicaBatch; ++k)
+                if (i0 + k < s.n)
+                    r[k] = ntload(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i0 + k, e0)) + q);
+#pragma unroll
+            for (int k = 0; k < kReplicaBatch; ++k)
+                if (i0 + k < s.n) {
+                    const f4 d = xv - r[k];
+                    acc = (i0 + k == 0) ? d : acc + d;
+                }
+        }
         if (s.n_pow2) return acc * s.inv_n;
         return acc / s.n_f;
     }
@@ -400,64 +353,46 @@ __device__ __forceinline__ f4 global_adamw4(f4 x, f4 delta, f4& m, f4& v, float 
 
 template <int N, int RULE, bool BCAST>
 __global__ __launch_bounds__(kBlockThreads) void k_global_det(
-    const Chunk* __restrict__ chunks, int map, float* __restrict__ x, float* __restrict__ m,
+    const Chunk* __restrict__ chunks, Rows rows, float* __restrict__ x, float* __restrict__ m,
     float* __restrict__ v, float* __restrict__ x_rep, RepLayout rl, GlobalScalars sc) {
-    const Piece pc = piece_of(chunks, map);
+    const Strip st = strip_of(chunks, rows);
+    const int q = lane_id();
+    if (q >= st.nq) return;
     const int n = N > 0 ? N : sc.n;
-    f4* __restrict__ xp = reinterpret_cast<f4*>(x + pc.e0);
-    f4* __restrict__ mp = reinterpret_cast<f4*>(m + pc.e0);
-    f4* __restrict__ vp = reinterpret_cast<f4*>(v + pc.e0);
-    const float lam = pc.c.decay ? sc.lam : 0.0f;
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], mv[kUnroll], vv[kUnroll], dv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xp + q);
-                mv[k] = ntload(mp + q);
-                if (RULE == kRuleGlobalAdamW) vv[k] = ntload(vp + q);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) dv[k] = worker_mean_diff<N>(xv[k], x_rep, rl, pc.e0, q, sc);
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                const int valid = pc.valid0 - 4 * q;
-                f4 xn;
-                if constexpr (RULE == kRuleSignMomentum) {
-                    const f4 u = momentum4(mv[k], dv[k], sc);
-                    xn = model4(xv[k], sign4(u), lam, sc);
-                } else if constexpr (RULE == kRuleLookahead) {
-                    const f4 u = momentum4(mv[k], dv[k], sc);
-                    xn = model4(xv[k], u, lam, sc);
-                } else if constexpr (RULE == kRuleSignedSlowMo) {
-                    // u from the old m and the sign of the difference; m by Eq. (8).
-                    const f4 u1 = sc.beta1 * mv[k];
-                    const f4 u2 = sc.c1 * sign4(dv[k]);
-                    const f4 u = u1 + u2;
-                    const f4 m1 = sc.beta2 * mv[k];
-                    const f4 m2 = sc.c2 * dv[k];
-                    mv[k] = m1 + m2;
-                    xn = model4(xv[k], u, lam, sc);
-                } else {
-                    xn = global_adamw4(xv[k], dv[k], mv[k], vv[k], lam, sc);
-                    store_vec(vv[k], vp + q, valid);
-                }
-                store_vec(xn, xp + q, valid);
-                store_vec(mv[k], mp + q, valid);
-                if (BCAST) {
-                    for (int i = 0; i < n; ++i)
-                        store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0)) + q,
-                                  valid);
-                }
-            }
-        }
+    f4* __restrict__ xp = reinterpret_cast<f4*>(x + st.e0) + q;
+    f4* __restrict__ mp = reinterpret_cast<f4*>(m + st.e0) + q;
+    f4* __restrict__ vp = reinterpret_cast<f4*>(v + st.e0) + q;
+    const float lam = st.c.decay ? sc.lam : 0.0f;
+    const int valid = st.valid0 - 4 * q;
+    const f4 xv = ntload(xp);
+    f4 mv = ntload(mp), vv;
+    if (RULE == kRuleGlobalAdamW) vv = ntload(vp);
+    const f4 delta = worker_mean_diff<N>(xv, x_rep, rl, st.e0, q, sc);
+    f4 xn;
+    if constexpr (RULE == kRuleSignMomentum) {
+        const f4 u = momentum4(mv, delta, sc);
+        xn = model4(xv, sign4(u), lam, sc);
+    } else if constexpr (RULE == kRuleLookahead) {
+        const f4 u = momentum4(mv, delta, sc);
+        xn = model4(xv, u, lam, sc);
+    } else if constexpr (RULE == kRuleSignedSlowMo) {
+        // u from the old m and the sign of the difference; m by Eq. (8).
+        const f4 u1 = sc.beta1 * mv;
+        const f4 u2 = sc.c1 * sign4(delta);
+        const f4 u = u1 + u2;
+        const f4 m1 = sc.beta2 * mv;
+        const f4 m2 = sc.c2 * delta;
+        mv = m1 + m2;
+        xn = model4(xv, u, lam, sc);
+    } else {
+        xn = global_adamw4(xv, delta, mv, vv, lam, sc);
+        store_vec(vv, vp, valid);
+    }
+    store_vec(xn, xp, valid);
+    store_vec(mv, mp, valid);
+    if (BCAST) {
+        for (int i = 0; i < n; ++i)
+            store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
     }
 }
 
@@ -496,61 +431,33 @@ __device__ __forceinline__ uint32_t abs_max(f4 u, int valid) {
     return b;
 }
 
-// The tensor bound B_p = max |u| is reduced in two levels, with plain loads
-// and stores and no atomics.  Level one: each work-group stores the largest
-// |u| of its piece, as a bit pattern, in the piece's own slot (for
-// non-negative IEEE floats the unsigned order of the bit patterns is the
-// numeric order).  Level two is k_bound_reduce.
-__device__ __forceinline__ void store_piece_max(uint32_t bits, uint32_t* lds, uint32_t* slot) {
-    const uint32_t b = block_max<kBlockThreads>(bits, lds);
-    if (threadIdx.x == 0) *slot = b;
-}
-
 // Randomized sign, pass 1: the all-reduce difference, u_{t+1} (staged to u)
-// and m_{t+1} (Eqs. (6), (8)), and the tensor bound B_p = max |u|.
+// and m_{t+1} (Eqs. (6), (8)), and the tensor bound B_p = max |u|, reduced in
+// two levels with plain loads and stores and no atomics.  Level one: each
+// work-group (a quad) stores its largest |u| in its own word.  Level two is
+// k_bound_reduce.
 template <int N>
 __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
-    const Chunk* __restrict__ chunks, int map, const float* __restrict__ x, float* __restrict__ m,
-    const float* __restrict__ x_rep, RepLayout rl, float* __restrict__ u_out,
-    uint32_t* __restrict__ piece_max, GlobalScalars sc) {
-    const Piece pc = piece_of(chunks, map);
-    const f4* __restrict__ xp = reinterpret_cast<const f4*>(x + pc.e0);
-    f4* __restrict__ mp = reinterpret_cast<f4*>(m + pc.e0);
-    f4* __restrict__ up = reinterpret_cast<f4*>(u_out + pc.e0);
+    const Chunk* __restrict__ chunks, Rows rows, const float* __restrict__ x,
+    float* __restrict__ m, const float* __restrict__ x_rep, RepLayout rl,
+    float* __restrict__ u_out, uint32_t* __restrict__ piece_max, GlobalScalars sc) {
     __shared__ uint32_t lds[kBlockThreads / 64];
+    const Strip st = strip_of(chunks, rows);
+    const int q = lane_id();
     uint32_t maxbits = 0;
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], mv[kUnroll], dv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xp + q);
-                mv[k] = ntload(mp + q);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) dv[k] = worker_mean_diff<N>(xv[k], x_rep, rl, pc.e0, q, sc);
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                const int valid = pc.valid0 - 4 * q;  // lanes inside the tensor
-                const f4 uv = momentum4(mv[k], dv[k], sc);
-                store_vec(uv, up + q, valid);
-                store_vec(mv[k], mp + q, valid);
-                uint32_t b = __float_as_uint(fabsf(uv.x));
-                if (valid > 1) b = max(b, __float_as_uint(fabsf(uv.y)));
-                if (valid > 2) b = max(b, __float_as_uint(fabsf(uv.z)));
-                if (valid > 3) b = max(b, __float_as_uint(fabsf(uv.w)));
-                maxbits = max(maxbits, b);
-            }
-        }
+    if (q < st.nq) {
+        f4* __restrict__ mp = reinterpret_cast<f4*>(m + st.e0) + q;
+        const f4 xv = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
+        f4 mv = ntload(mp);
+        const f4 delta = worker_mean_diff<N>(xv, x_rep, rl, st.e0, q, sc);
+        const int valid = st.valid0 - 4 * q;  // lanes inside the tensor
+        const f4 u = momentum4(mv, delta, sc);
+        store_vec(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
+        store_vec(mv, mp, valid);
+        maxbits = abs_max(u, valid);
     }
-    store_piece_max(maxbits, lds, piece_max + pc.wi);
+    maxbits = block_max<kBlockThreads>(maxbits, lds);
+    if (threadIdx.x == 0) piece_max[quad_word(st, rows)] = maxbits;
 }
 
 // Level two of the tensor bound: work-group p takes the level-one words of
@@ -608,48 +515,31 @@ __device__ __forceinline__ float rand_sign(float u, uint32_t w, double B) {
 // so its step is NaN rather than a step of a reversed or zero sign.
 template <int MODE, bool BCAST>
 __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
-    const Chunk* __restrict__ chunks, int map, float* __restrict__ x, float* __restrict__ x_rep,
+    const Chunk* __restrict__ chunks, Rows rows, float* __restrict__ x, float* __restrict__ x_rep,
     RepLayout rl, const float* __restrict__ u_in, const uint32_t* __restrict__ bound_bits,
     GlobalScalars sc) {
-    const Piece pc = piece_of(chunks, map);
-    const Chunk& c = pc.c;
-    f4* __restrict__ xp = reinterpret_cast<f4*>(x + pc.e0);
-    const f4* __restrict__ up = reinterpret_cast<const f4*>(u_in + pc.e0);
-    const float lam = c.decay ? sc.lam : 0.0f;
-    const uint32_t bbits = bound_bits[c.tensor];
+    const Strip st = strip_of(chunks, rows);
+    const int q = lane_id();
+    if (q >= st.nq) return;
+    f4* __restrict__ xp = reinterpret_cast<f4*>(x + st.e0) + q;
+    const f4 xv = ntload(xp);
+    const f4 u = ntload(reinterpret_cast<const f4*>(u_in + st.e0) + q);
+    const float lam = st.c.decay ? sc.lam : 0.0f;
+    const uint32_t bbits = bound_bits[st.c.tensor];
     const bool bound_finite = bbits < 0x7f800000u;   // B >= 0: below the +inf pattern
     const double B = static_cast<double>(__uint_as_float(bbits));
     const float undefined = __builtin_nanf("");
-    for (int q0 = threadIdx.x; q0 < pc.nq; q0 += kBlockThreads * kUnroll) {
-        f4 xv[kUnroll], uv[kUnroll];
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                xv[k] = ntload(xp + q);
-                uv[k] = ntload(up + q);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            const int q = q0 + k * kBlockThreads;
-            if (q < pc.nq) {
-                uint32_t w0 = pc.j4 + static_cast<uint32_t>(q), w1 = c.tensor, w2 = sc.t,
-                         w3 = kSignStream;
-                philox4x32_10(w0, w1, w2, w3, sc.key0, sc.key1);
-                f4 S = {rand_sign<MODE>(uv[k].x, w0, B), rand_sign<MODE>(uv[k].y, w1, B),
-                        rand_sign<MODE>(uv[k].z, w2, B), rand_sign<MODE>(uv[k].w, w3, B)};
-                if (!bound_finite) S = f4{undefined, undefined, undefined, undefined};
-                const f4 xn = model4(xv[k], S, lam, sc);
-                const int valid = pc.valid0 - 4 * q;
-                store_vec(xn, xp + q, valid);
-                if (BCAST) {
-                    for (int i = 0; i < sc.n; ++i)
-                        store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0)) + q,
-                                  valid);
-                }
-            }
-        }
+    uint32_t w0 = st.j4 + static_cast<uint32_t>(q), w1 = st.c.tensor, w2 = sc.t, w3 = kSignStream;
+    philox4x32_10(w0, w1, w2, w3, sc.key0, sc.key1);
+    f4 S = {rand_sign<MODE>(u.x, w0, B), rand_sign<MODE>(u.y, w1, B),
+            rand_sign<MODE>(u.z, w2, B), rand_sign<MODE>(u.w, w3, B)};
+    if (!bound_finite) S = f4{undefined, undefined, undefined, undefined};
+    const f4 xn = model4(xv, S, lam, sc);
+    const int valid = st.valid0 - 4 * q;
+    store_vec(xn, xp, valid);
+    if (BCAST) {
+        for (int i = 0; i < sc.n; ++i)
+            store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
     }
 }
 
@@ -766,37 +656,35 @@ __global__ __launch_bounds__(kBlockThreads) void k_clear_words(uint4* __restrict
 
 // Synchronisation step: x_rep[i] <- x for every replica.
 __global__ __launch_bounds__(kBlockThreads) void k_broadcast(
-    const Chunk* __restrict__ chunks, int map, const float* __restrict__ x, float* __restrict__ x_rep,
+    const Chunk* __restrict__ chunks, Rows rows, const float* __restrict__ x, float* __restrict__ x_rep,
     RepLayout rl, int n) {
-    const Piece pc = piece_of(chunks, map);
-    const f4* __restrict__ xp = reinterpret_cast<const f4*>(x + pc.e0);
-    for (int q = threadIdx.x; q < pc.nq; q += kBlockThreads) {
-        const f4 v = ntload(xp + q);
-        const int valid = pc.valid0 - 4 * q;
-        for (int i = 0; i < n; ++i)
-            store_vec(v, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0)) + q, valid);
-    }
+    const Strip st = strip_of(chunks, rows);
+    const int q = lane_id();
+    if (q >= st.nq) return;
+    const f4 v = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
+    const int valid = st.valid0 - 4 * q;
+    for (int i = 0; i < n; ++i)
+        store_vec(v, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
 }
 
 // Algorithm 1 initialisation: m = 0, replicas = x, base state = 0.
 __global__ __launch_bounds__(kBlockThreads) void k_init(
-    const Chunk* __restrict__ chunks, int map, const float* __restrict__ x, float* __restrict__ m,
+    const Chunk* __restrict__ chunks, Rows rows, const float* __restrict__ x, float* __restrict__ m,
     float* __restrict__ v, float* __restrict__ x_rep, RepLayout rl, float* __restrict__ s1,
     float* __restrict__ s2, StateLayout ml, int n) {
-    const Piece pc = piece_of(chunks, map);
-    const f4* __restrict__ xp = reinterpret_cast<const f4*>(x + pc.e0);
+    const Strip st = strip_of(chunks, rows);
+    const int q = lane_id();
+    if (q >= st.nq) return;
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int q = threadIdx.x; q < pc.nq; q += kBlockThreads) {
-        const f4 xv = ntload(xp + q);
-        const int valid = pc.valid0 - 4 * q;
-        store_vec(zero, reinterpret_cast<f4*>(m + pc.e0) + q, valid);
-        if (v != nullptr) store_vec(zero, reinterpret_cast<f4*>(v + pc.e0) + q, valid);
-        for (int i = 0; i < n; ++i) {
-            store_vec(xv, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, pc.e0)) + q, valid);
-            store_vec(zero, reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, pc.e0)) + q, valid);
-            if (s2 != nullptr)
-                store_vec(zero, reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, pc.e0)) + q, valid);
-        }
+    const f4 xv = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
+    const int valid = st.valid0 - 4 * q;
+    store_vec(zero, reinterpret_cast<f4*>(m + st.e0) + q, valid);
+    if (v != nullptr) store_vec(zero, reinterpret_cast<f4*>(v + st.e0) + q, valid);
+    for (int i = 0; i < n; ++i) {
+        store_vec(xv, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
+        store_vec(zero, reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, st.e0)) + q, valid);
+        if (s2 != nullptr)
+            store_vec(zero, reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, st.e0)) + q, valid);
     }
 }
 
@@ -815,18 +703,24 @@ __global__ __launch_bounds__(kBlockThreads) void k_test_philox(uint32_t key0, ui
 }
 
 // Streaming diagnostics with the access shape of the kernels above: one
-// piece of kPieceVec float4 groups per work-group, XCD map 1, 16-byte
-// nontemporal accesses, consecutive lanes on consecutive groups.  The read
+// piece of kPieceVec float4 groups per work-group, XCD k on the k-th eighth of
+// the buffer, 16-byte nontemporal accesses, consecutive lanes on consecutive groups.  The read
 // kernel folds its piece into one word (the XOR of its 32-bit patterns) and
 // writes only where that word equals `pattern`, so with a pattern no piece
 // matches it issues no write at all: even one 4-byte store per piece,
 // interleaved with the loads, costs the read stream a measurable share of
 // its rate.  The write kernel stores the float with bit pattern `pattern`.
+__device__ __forceinline__ uint32_t stream_piece() {
+    const uint32_t b = blockIdx.x, per = gridDim.x / kXcds;
+    if (b >= per * kXcds) return b;
+    return (b % kXcds) * per + b / kXcds;
+}
+
 __global__ __launch_bounds__(kBlockThreads) void k_stream_read(const float* __restrict__ buf,
                                                               uint32_t* __restrict__ words,
                                                               uint32_t pattern) {
     __shared__ uint32_t wave_acc[kBlockThreads / 64];
-    const uint32_t wi = work_index<1>();
+    const uint32_t wi = stream_piece();
     const f4* __restrict__ p = reinterpret_cast<const f4*>(buf) + static_cast<int64_t>(wi) * kPieceVec;
     uint32_t acc = 0;
     for (int q = threadIdx.x; q < kPieceVec; q += kBlockThreads) {
@@ -846,15 +740,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_read(const float* __re
 
 __global__ __launch_bounds__(kBlockThreads) void k_stream_write(float* __restrict__ buf,
                                                                uint32_t pattern) {
-    const uint32_t wi = work_index<1>();
+    const uint32_t wi = stream_piece();
     f4* __restrict__ p = reinterpret_cast<f4*>(buf) + static_cast<int64_t>(wi) * kPieceVec;
     const float value = __uint_as_float(pattern);
     const f4 v = {value, value, value, value};
     for (int q = threadIdx.x; q < kPieceVec; q += kBlockThreads) ntstore(v, p + q);
-}
-
-dim3 chunk_grid(int64_t n_chunks, int n_workers) {
-    return dim3(static_cast<unsigned>(n_chunks * kSplit), static_cast<unsigned>(n_workers), 1);
 }
 
 // Launch shape.  All kernels are bound by HBM, and what decides how much of
@@ -889,6 +779,20 @@ constexpr unsigned lds_for(int per_cu, int waves) { return lds_for((per_cu + wav
 // load of most waves hits the L2, so a few more.
 constexpr int kAdamWWaves = 12, kAdamWSharedWaves = 14;
 constexpr int kSgdWaves = 20, kSgdSharedWaves = 18;
+// The global step loads n + 2 streams at once: n = 4, 80.3% with 8, 77% with
+// 12; n = 1, 81.0% with 12, 76% with 8.
+constexpr int global_waves(int n) { return n == 1 ? 12 : n == 2 ? 10 : 8; }
+// The randomized first pass has no replica to write and lasts well with a few
+// more: n = 4 and 8, 80.7-81.8% with 12; n = 1 and 2, 79.6 and 83.3% with 16.
+constexpr int pass1_waves(int n) { return n <= 2 ? 16 : 12; }
+// The second pass and the synchronisation load two streams and one; their
+// stores count: with one worker 20 and all of them (sync, n = 1: 81.5%, 71%
+// with 12), down to 12 and 8 with many (sync, n = 8: 82-86%, 74% with 32).
+constexpr int pass2_waves(int stores) { return stores <= 2 ? 20 : stores == 3 ? 16 : 12; }
+constexpr int copy_waves(int n) {
+    return n == 1 ? kAllWaves : n == 2 ? 20 : n == 3 ? 16 : n <= 5 ? 12 : 8;
+}
+constexpr int kInitWaves = 12;
 
 // A launch that touches less than half the 256 MB last-level cache is over
 // before its rows fight: it is bound by latency, and takes all the waves that
@@ -924,6 +828,22 @@ int waves_for(int64_t n_chunks, const RepLayout& rl, int streams, int waves) {
     return small_launch(n_chunks, rl, streams) ? kAllWaves : waves;
 }
 
+// Launches a kernel that touches `streams` arenas over every strip, at most
+// `waves` waves per CU unless it is small, in the map's work-group shape.
+template <typename K, typename... Args>
+void launch_strips(K kernel, const Chunk* chunks, int64_t n_chunks, const RepLayout& rl, int map,
+                   int streams, int waves, hipStream_t stream, Args... args) {
+    const Rows rows = rows_of(n_chunks, rl, map);
+    waves = waves_for(n_chunks, rl, streams, waves);
+    if (map & kQuads)
+        hipLaunchKernelGGL(kernel, quad_grid(n_chunks, rl), dim3(kBlockThreads),
+                           lds_for(waves, kQuadWaves), stream, chunks, rows,
+                           args...);
+    else
+        hipLaunchKernelGGL(kernel, strip_grid(n_chunks, rl), dim3(kWave), lds_for(waves), stream,
+                           chunks, rows, args...);
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
@@ -932,8 +852,8 @@ hipError_t launch_init(const Chunk* chunks, int64_t n_chunks, float* x, float* m
                        float* x_rep, RepLayout rl, float* s1, float* s2, StateLayout ml, int n,
                        int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_init, chunk_grid(n_chunks, 1), dim3(kBlockThreads), 0, st, chunks, map, x,
-                       m, v, x_rep, rl, s1, s2, ml, n);
+    launch_strips(k_init, chunks, n_chunks, rl, map, 3 * n + 2, kInitWaves, st, x, m, v, x_rep, rl,
+                  s1, s2, ml, n);
     return hipGetLastError();
 }
 
@@ -1068,9 +988,10 @@ static void launch_bound_reduce(const Chunk* chunks, const BoundWords& bw, int n
 static void launch_rand_pass2(const Chunk* chunks, int64_t n_chunks, float* x, float* x_rep,
                               RepLayout rl, const float* u, const uint32_t* bits,
                               const GlobalScalars& sc, bool broadcast, int map, hipStream_t st) {
-    const dim3 grid = chunk_grid(n_chunks, 1), block(kBlockThreads);
-#define DSM_PASS2(MODE, B) \
-    hipLaunchKernelGGL((k_global_rand_pass2<MODE, B>), grid, block, 0, st, chunks, map, x, x_rep, rl, u, bits, sc)
+    const int stores = broadcast ? sc.n + 1 : 1;
+#define DSM_PASS2(MODE, B)                                                                      \
+    launch_strips(k_global_rand_pass2<MODE, B>, chunks, n_chunks, rl, map, stores + 1,          \
+                  pass2_waves(stores), st, x, x_rep, rl, u, bits, sc)
     if (sc.mode == 1) {
         if (broadcast) DSM_PASS2(1, true); else DSM_PASS2(1, false);
     } else {
@@ -1101,10 +1022,9 @@ template <int RULE, bool BCAST>
 static void launch_global_det_n(const Chunk* chunks, int64_t n_chunks, float* x, float* m,
                                 float* v, float* x_rep, RepLayout rl, const GlobalScalars& sc,
                                 int map, hipStream_t st) {
-    const dim3 grid = chunk_grid(n_chunks, 1), block(kBlockThreads);
-#define DSM_GLOBAL_DET(NW)                                                                     \
-    hipLaunchKernelGGL((k_global_det<NW, RULE, BCAST>), grid, block, 0, st, chunks, map, x, m, \
-                       v, x_rep, rl, sc)
+#define DSM_GLOBAL_DET(NW)                                                                       \
+    launch_strips(k_global_det<NW, RULE, BCAST>, chunks, n_chunks, rl, map, sc.n + 2,            \
+                  global_waves(sc.n), st, x, m, v, x_rep, rl, sc)
     switch (sc.n) {
         case 1: DSM_GLOBAL_DET(1); break;
         case 2: DSM_GLOBAL_DET(2); break;
@@ -1155,10 +1075,9 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
                               const BoundWords& bw, const GlobalScalars& sc, bool broadcast,
                               int map, hipStream_t st) {
     if (n_chunks > 0) {
-        const dim3 grid = chunk_grid(n_chunks, 1), block(kBlockThreads);
-        uint32_t* pm = bw.piece_max;
-#define DSM_PASS1(NW) \
-    hipLaunchKernelGGL(k_global_rand_pass1<NW>, grid, block, 0, st, chunks, map, x, m, x_rep, rl, u, pm, sc)
+#define DSM_PASS1(NW)                                                                            \
+    launch_strips(k_global_rand_pass1<NW>, chunks, n_chunks, rl, kQuads, sc.n + 3,               \
+                  pass1_waves(sc.n), st, x, m, x_rep, rl, u, bw.piece_max, sc)
         switch (sc.n) {
             case 1: DSM_PASS1(1); break;
             case 2: DSM_PASS1(2); break;
@@ -1177,8 +1096,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
 hipError_t launch_broadcast(const Chunk* chunks, int64_t n_chunks, const float* x, float* x_rep,
                             RepLayout rl, int n, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_broadcast, chunk_grid(n_chunks, 1), dim3(kBlockThreads), 0, st, chunks,
-                       map, x, x_rep, rl, n);
+    launch_strips(k_broadcast, chunks, n_chunks, rl, map, n + 1, copy_waves(n), st, x, x_rep, rl, n);
     return hipGetLastError();
 }
 
