@@ -52,10 +52,12 @@ struct RepLayout {
     int64_t block_stride;
     int64_t copy_stride;
     int32_t shift;
-    // Of the problem, not of the buffer: 0, or where most strip groups of its
-    // chunks hold no elements (many tensors far shorter than a chunk), the
-    // number of those that do; its launches then go over these only.
-    int32_t groups;
+    // Of the problem, not of the buffer.  groups: 0, or where most strip groups
+    // of its chunks hold no elements (many tensors far shorter than a chunk),
+    // the number of those that do; its launches then go over these only.
+    // cached: its arenas are small enough to stay in the caches between calls.
+    uint32_t groups : 31;
+    uint32_t cached : 1;
 };
 // Sparse from half the groups empty on.  A wave of a sparse launch searches for
 // its chunk, ~1 us; the waves it saves cost their dispatch (125 tensors of 64K
@@ -65,14 +67,17 @@ struct RepLayout {
 constexpr bool sparse_chunks(int64_t groups, int64_t n_chunks) {
     return 2 * groups <= n_chunks * (kStrips / kGroupStrips);
 }
+// Three eighths of the 256 MB last-level cache: problems of 106 MB taking turns
+// already lose 2% to plain accesses.
+constexpr int64_t kCachedBytes = int64_t(96) << 20;
 // n contiguous copies of d_pad elements.
-inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0}; }
+inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0, 0}; }
 // n copies interleaved in 64 KiB blocks.
 inline RepLayout blocked_copies(int n) {
-    return RepLayout{int64_t(n) * kRepBlockElems, kRepBlockElems, kRepBlockShift, 0};
+    return RepLayout{int64_t(n) * kRepBlockElems, kRepBlockElems, kRepBlockShift, 0, 0};
 }
 // Every copy is the same single buffer (stale replicas read the global x).
-inline RepLayout single_copy() { return RepLayout{0, 0, 62, 0}; }
+inline RepLayout single_copy() { return RepLayout{0, 0, 62, 0, 0}; }
 
 // The replicas and their state in one allocation (dsm_problem.replica_layout =
 // DSM_REPLICAS_STATE_BLOCKED): 16 KiB blocks, and block b holds the n x_rep
@@ -84,7 +89,7 @@ constexpr int64_t kStateBlockElems = int64_t(1) << kStateBlockShift;
 static_assert(kStateBlockElems % kPieceElems == 0, "a state block must hold whole pieces");
 inline RepLayout state_blocked_copies(int n, int buffers) {
     return RepLayout{int64_t(buffers) * n * kStateBlockElems, kStateBlockElems, kStateBlockShift,
-                     0};
+                     0, 0};
 }
 
 // Where the gradient and the base-optimizer moments of worker i keep their
