@@ -217,6 +217,7 @@ struct BoundWords {
     uint32_t* bits;         // [n_tensors] B_p, fp32 bit patterns
     uint32_t* piece_max;    // [n_chunks * kSplit] level one: max |u| of each piece
     const int32_t* chunk0;  // [n_tensors + 1] first chunk of each tensor; last = n_chunks
+    int64_t max_words;      // most level-one words of a tensor
 };
 
 // Arguments of the fused last-local-step + global-step launch.

@@ -471,35 +471,48 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
     if (threadIdx.x == 0) piece_max[quad_word(st, rows)] = maxbits;
 }
 
-// Level two of the tensor bound: work-group p takes the level-one words of
-// tensor p, kSplit for each of its chunks from chunk0[p] * kSplit on, and
-// stores their largest in bound_bits[p]; an empty tensor has none and gets 0.
-// Over sparse chunks only the words of the strip groups that hold elements
-// have been written: a prefix, since all chunks of a tensor but the last are
-// full.
+// The level-one words of tensor p: kSplit for each of its chunks.  Over sparse
+// chunks only the words of the strip groups that hold elements have been
+// written: a prefix, since all chunks of a tensor but the last are full.
+struct BoundRange {
+    int64_t lo, n;  // lo a multiple of 4 words, which start 256-byte aligned
+};
+__device__ __forceinline__ BoundRange bound_range(const Chunk* __restrict__ chunks,
+                                                  const int32_t* __restrict__ chunk0, uint32_t p,
+                                                  bool sparse) {
+    const int32_t c_lo = chunk0[p], c_hi = chunk0[p + 1];
+    BoundRange r{static_cast<int64_t>(c_lo) * kSplit, static_cast<int64_t>(c_hi - c_lo) * kSplit};
+    if (sparse && r.n > 0)
+        r.n -= kSplit - (chunks[c_hi - 1].len + kGroupElems - 1) / kGroupElems * kGroupPieces;
+    return r;
+}
+
+// Largest of every THREADS-th four of r's words from thread t's on.
+template <int THREADS>
+__device__ __forceinline__ uint32_t max_words(const uint32_t* __restrict__ piece_max,
+                                              const BoundRange& r, int t) {
+    uint32_t b = 0;
+    const uint4* __restrict__ v = reinterpret_cast<const uint4*>(piece_max + r.lo);
+#pragma unroll 4
+    for (int64_t i = t; i < r.n / 4; i += THREADS) {
+        const uint4 w = v[i];
+        b = max(b, max(max(w.x, w.y), max(w.z, w.w)));
+    }
+    const int64_t i = r.n / 4 * 4 + t;
+    return i < r.n ? max(b, piece_max[r.lo + i]) : b;
+}
+
+// Level two of the tensor bound: work-group p stores the largest level-one
+// word of tensor p in bound_bits[p]; an empty tensor has none and gets 0.
 constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void k_bound_reduce(
     const Chunk* __restrict__ chunks, const uint32_t* __restrict__ piece_max,
     const int32_t* __restrict__ chunk0, uint32_t* __restrict__ bound_bits, bool sparse) {
     __shared__ uint32_t lds[kReduceThreads / 64];
-    const int p = blockIdx.x;
-    const int32_t c_lo = chunk0[p], c_hi = chunk0[p + 1];
-    const int64_t lo = static_cast<int64_t>(c_lo) * kSplit;
-    int64_t n = static_cast<int64_t>(c_hi - c_lo) * kSplit;
-    if (sparse && n > 0)
-        n -= kSplit - (chunks[c_hi - 1].len + kGroupElems - 1) / kGroupElems * kGroupPieces;
-    uint32_t b = 0;
-    // lo is a multiple of 4 slots, and the slots start 256-byte aligned.
-    const uint4* __restrict__ v = reinterpret_cast<const uint4*>(piece_max + lo);
-#pragma unroll 4
-    for (int64_t i = threadIdx.x; i < n / 4; i += kReduceThreads) {
-        const uint4 w = v[i];
-        b = max(b, max(max(w.x, w.y), max(w.z, w.w)));
-    }
-    const int64_t i = n / 4 * 4 + threadIdx.x;
-    if (i < n) b = max(b, piece_max[lo + i]);
-    b = block_max<kReduceThreads>(b, lds);
-    if (threadIdx.x == 0) bound_bits[p] = b;
+    const BoundRange r = bound_range(chunks, chunk0, blockIdx.x, sparse);
+    const uint32_t b = block_max<kReduceThreads>(
+        max_words<kReduceThreads>(piece_max, r, static_cast<int>(threadIdx.x)), lds);
+    if (threadIdx.x == 0) bound_bits[blockIdx.x] = b;
 }
 
 // S_r(u) of Eq. (9) (MODE 1) or Eq. (10) (MODE 2) for one element, given the
@@ -524,19 +537,33 @@ __device__ __forceinline__ float rand_sign(float u, uint32_t w, double B) {
 // Section 3.1 defines S_r only for a finite bound: a tensor whose bound is
 // NaN or infinite (it holds a non-finite u) gets S = NaN at every element,
 // so its step is NaN rather than a step of a reversed or zero sign.
-template <int MODE, bool BCAST, int POLICY>
+//
+// FOLD: level two of the bound as well.  Each wave takes the maximum of its
+// tensor's words itself, and the wave of the tensor's first strip stores it.
+template <int MODE, bool BCAST, int POLICY, bool FOLD>
 __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
     const Chunk* __restrict__ chunks, Rows rows, float* __restrict__ x, float* __restrict__ x_rep,
-    RepLayout rl, const float* __restrict__ u_in, const uint32_t* __restrict__ bound_bits,
-    GlobalScalars sc) {
+    RepLayout rl, const float* __restrict__ u_in, BoundWords bw, GlobalScalars sc) {
     const Strip st = strip_of(chunks, rows);
     const int q = lane_id();
-    if (q >= st.nq) return;
+    if (st.nq == 0) return;
+    const bool on = q < st.nq;
     f4* __restrict__ xp = reinterpret_cast<f4*>(x + st.e0) + q;
-    const f4 xv = load<POLICY>(xp);
-    const f4 u = load<POLICY>(reinterpret_cast<const f4*>(u_in + st.e0) + q);
+    f4 xv, u;
+    if (on) {
+        xv = load<POLICY>(xp);
+        u = load<POLICY>(reinterpret_cast<const f4*>(u_in + st.e0) + q);
+    }
+    uint32_t bbits;
+    if constexpr (FOLD) {
+        const BoundRange r = bound_range(chunks, bw.chunk0, st.c.tensor, rows.sparse_chunks > 0);
+        bbits = wave_max(max_words<kWave>(bw.piece_max, r, q));
+        if (st.j4 == 0 && q == 0) bw.bits[st.c.tensor] = bbits;
+    } else {
+        bbits = bw.bits[st.c.tensor];
+    }
+    if (!on) return;
     const float lam = st.c.decay ? sc.lam : 0.0f;
-    const uint32_t bbits = bound_bits[st.c.tensor];
     const bool bound_finite = bbits < 0x7f800000u;   // B >= 0: below the +inf pattern
     const double B = static_cast<double>(__uint_as_float(bbits));
     const float undefined = __builtin_nanf("");
@@ -1004,28 +1031,46 @@ static void launch_round_end_base(const Chunk* chunks, int64_t n_chunks, const R
         launch_round_end_kind<BASE, 2>(chunks, n_chunks, a, st);
 }
 
-// Level two of the tensor bound, after a first pass has stored its piece
-// maxima.  Also run with no chunks at all, so that every bound is written.
-static void launch_bound_reduce(const Chunk* chunks, const BoundWords& bw, int n_tensors,
-                                bool sparse, hipStream_t st) {
-    hipLaunchKernelGGL(k_bound_reduce, dim3(static_cast<unsigned>(n_tensors)),
-                       dim3(kReduceThreads), 0, st, chunks, bw.piece_max, bw.chunk0, bw.bits,
-                       sparse);
+// Whether the second pass takes the tensor bounds itself.  Every wave then
+// reads its tensor's words, through the L2: worth it for as long as that is
+// less time than a launch, ~4.5 us.  At 14 MB of such reads a round of 2M
+// elements takes 40.0 us against 42.1 us, at 31 MB the two are equal, at 66 MB
+// the reads cost 2% of a 40 us round.
+static bool fold_bound(int64_t n_chunks, const RepLayout& rl, const BoundWords& bw) {
+    constexpr int64_t kMaxFoldBytes = int64_t(32) << 20;
+    return groups_of(n_chunks, rl) * kGroupStrips * bw.max_words * 4 <= kMaxFoldBytes;
 }
 
-static void launch_rand_pass2(const Chunk* chunks, int64_t n_chunks, float* x, float* x_rep,
-                              RepLayout rl, const float* u, const uint32_t* bits,
-                              const GlobalScalars& sc, bool broadcast, int map, hipStream_t st) {
+// The randomized sign after its first pass: level two of the tensor bound
+// (also with no chunks at all, so that every bound is written) and the second
+// pass.
+static void launch_rand_rest(const Chunk* chunks, int64_t n_chunks, int n_tensors, float* x,
+                             float* x_rep, const RepLayout& rl, const float* u,
+                             const BoundWords& bw, const GlobalScalars& sc, bool broadcast, int map,
+                             hipStream_t st) {
+    const bool fold = n_chunks > 0 && fold_bound(n_chunks, rl, bw);
+    if (n_tensors > 0 && !fold)
+        hipLaunchKernelGGL(k_bound_reduce, dim3(static_cast<unsigned>(n_tensors)),
+                           dim3(kReduceThreads), 0, st, chunks, bw.piece_max, bw.chunk0, bw.bits,
+                           rl.groups > 0);
+    if (n_chunks == 0) return;
     const int stores = broadcast ? sc.n + 1 : 1;
-#define DSM_PASS2(MODE, B)                                                                      \
-    launch_strips(rl.cached ? k_global_rand_pass2<MODE, B, kCached>                                \
-                            : k_global_rand_pass2<MODE, B, kStream>, chunks, n_chunks, rl, map, stores + 1,          \
-                  pass2_waves(stores), st, x, x_rep, rl, u, bits, sc)
+#define DSM_PASS2(MODE, B, POLICY, FOLD)                                                        \
+    launch_strips(k_global_rand_pass2<MODE, B, POLICY, FOLD>, chunks, n_chunks, rl, map,        \
+                  stores + 1, pass2_waves(stores), st, x, x_rep, rl, u, bw, sc)
+#define DSM_PASS2_POLICY(MODE, B)                                                               \
+    do {                                                                                        \
+        if (!fold && !rl.cached) DSM_PASS2(MODE, B, kStream, false);                            \
+        else if (!fold) DSM_PASS2(MODE, B, kCached, false);                                     \
+        else if (!rl.cached) DSM_PASS2(MODE, B, kStream, true);                                 \
+        else DSM_PASS2(MODE, B, kCached, true);                                                 \
+    } while (0)
     if (sc.mode == 1) {
-        if (broadcast) DSM_PASS2(1, true); else DSM_PASS2(1, false);
+        if (broadcast) DSM_PASS2_POLICY(1, true); else DSM_PASS2_POLICY(1, false);
     } else {
-        if (broadcast) DSM_PASS2(2, true); else DSM_PASS2(2, false);
+        if (broadcast) DSM_PASS2_POLICY(2, true); else DSM_PASS2_POLICY(2, false);
     }
+#undef DSM_PASS2_POLICY
 #undef DSM_PASS2
 }
 
@@ -1039,11 +1084,9 @@ hipError_t launch_round_end(const Chunk* chunks, int64_t n_chunks, int n_tensors
         else
             launch_round_end_base<kBaseSgd>(chunks, n_chunks, a, kind, st);
     }
-    if (randomized && n_tensors > 0)
-        launch_bound_reduce(chunks, a.bound, n_tensors, a.rl.groups > 0, st);
-    if (randomized && n_chunks > 0)
-        launch_rand_pass2(chunks, n_chunks, a.x, a.x_rep, a.rl, a.u, a.bound.bits, a.gs,
-                          broadcast, a.map_pass2, st);
+    if (randomized)
+        launch_rand_rest(chunks, n_chunks, n_tensors, a.x, a.x_rep, a.rl, a.u, a.bound, a.gs,
+                         broadcast, a.map_pass2, st);
     return hipGetLastError();
 }
 
@@ -1123,9 +1166,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
         }
 #undef DSM_PASS1
     }
-    if (n_tensors > 0) launch_bound_reduce(chunks, bw, n_tensors, rl.groups > 0, st);
-    if (n_chunks > 0)
-        launch_rand_pass2(chunks, n_chunks, x, x_rep, rl, u, bw.bits, sc, broadcast, map, st);
+    launch_rand_rest(chunks, n_chunks, n_tensors, x, x_rep, rl, u, bw, sc, broadcast, map, st);
     return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 // The runtime owns only host memory; every device buffer is the caller's.
 #include "dsm.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -24,7 +25,8 @@ struct dsm_ctx {
     dsm::RepLayout rep{};            // how x_rep holds the n replicas
     dsm::StateLayout ml{};           // how g_rep, s1_rep and s2_rep hold theirs
     dsm::XcdMaps maps{};             // XCD map of each kernel kind for this layout
-    std::vector<int32_t> chunk0;     // first chunk of each tensor, then n_chunks (host copy)
+    std::vector<int32_t> chunk0;     // host copy of the workspace's words from the bounds to the
+                                     // end of the tensor chunk index
     dsm_buffers buf{};
     dsm::Chunk* d_chunks = nullptr;
     dsm::BoundWords bound{};         // workspace words of the randomized sign's bound
@@ -467,8 +469,14 @@ dsm_status init_context(const dsm_problem* problem, const dsm_buffers* caller, d
     ctx->local_count.assign(ctx->n, 0);
     ctx->stale.assign(ctx->n, 0);
 
+    // The bounds, zero (an empty tensor's stays so), and the tensor chunk index,
+    // which follows them.
+    for (int i = 0; i < ctx->n_tensors; ++i)
+        ctx->bound.max_words = std::max<int64_t>(
+            ctx->bound.max_words, int64_t(ctx->chunk0[i + 1] - ctx->chunk0[i]) * dsm::kSplit);
+    ctx->chunk0.insert(ctx->chunk0.begin(), (L.chunk0_off - L.bounds_off) / sizeof(int32_t), 0);
     if (ctx->n_tensors > 0) {
-        hipError_t e = hipMemcpyAsync(const_cast<int32_t*>(ctx->bound.chunk0), ctx->chunk0.data(),
+        hipError_t e = hipMemcpyAsync(ctx->bound.bits, ctx->chunk0.data(),
                                       ctx->chunk0.size() * sizeof(int32_t),
                                       hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) {
