@@ -31,9 +31,8 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // kStream: nontemporal loads and stores, for arenas that have left every cache
 // before they are read again.
 // kShared: the same, but for a local step's starting point, which in the
-// interleaved order the n waves of one XCD read at about the same time: a
-// plain load leaves it in the XCD's L2 for the others, and x comes from HBM
-// once.
+// interleaved order the n workers read one soon after the other: a plain load
+// leaves it in the caches for the others, and x comes from HBM once.
 // kCached: plain loads and stores, for problems whose arenas are still in the
 // 256 MB last-level cache at the next call (RepLayout::cached): rounds of 1.1M
 // elements, n = 2, 27.8 us against 36.6 us with nontemporal ones; 8 x 128K,
@@ -165,15 +164,25 @@ __device__ __forceinline__ uint32_t quad_word(const Strip& st, const Rows& rows)
 
 // The strip and worker of a local step's wave.  Without kInterleaveWorkers in
 // the map the grid is (work-groups, workers) and runs worker by worker; with it
-// the grid is one row of strips x workers in which the eight strips of a
-// group, one per XCD, of one worker are followed by those of the next worker.
+// the grid is one row of strips x workers in which a turn of one worker is
+// followed by the same turn of the next: a strip group (eight strips, one per
+// XCD), or (WIDE, kWideTurns) kTurnGroups of them, the last turn maybe fewer.
+template <bool WIDE>
 __device__ __forceinline__ Strip local_strip(const Chunk* __restrict__ chunks, const Rows& rows,
                                              int worker0, int n_workers, int64_t& w) {
     const uint32_t b = blockIdx.x;
     if (rows.map & kInterleaveWorkers) {
         const uint32_t g = b / kGroupStrips, n = static_cast<uint32_t>(n_workers);
-        w = worker0 + static_cast<int64_t>(g % n);
-        return strip_at(chunks, rows, (g / n) * kGroupStrips + b % kGroupStrips);
+        uint32_t worker = g % n, group = g / n;
+        if (WIDE && (rows.map & kWideTurns)) {
+            const uint32_t turn = g / (kTurnGroups * n), r = g % (kTurnGroups * n);
+            const uint32_t size =
+                min(kTurnGroups, gridDim.x / kGroupStrips / n - turn * kTurnGroups);
+            worker = r / size;
+            group = turn * kTurnGroups + r % size;
+        }
+        w = worker0 + static_cast<int64_t>(worker);
+        return strip_at(chunks, rows, group * kGroupStrips + b % kGroupStrips);
     }
     w = worker0 + static_cast<int64_t>(blockIdx.y);
     return strip_of(chunks, rows);
@@ -219,7 +228,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_local_adamw(
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1,
     float* __restrict__ s2, StateLayout ml, int worker0, int n_workers, AdamScalars sc) {
     int64_t w;
-    const Strip st = local_strip(chunks, rows, worker0, n_workers, w);
+    const Strip st = local_strip<POLICY == kShared>(chunks, rows, worker0, n_workers, w);
     const int q = lane_id();
     if (q >= st.nq) return;
     f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
@@ -251,7 +260,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_local_sgdm(
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1, StateLayout ml,
     int worker0, int n_workers, SgdScalars sc) {
     int64_t w;
-    const Strip st = local_strip(chunks, rows, worker0, n_workers, w);
+    const Strip st = local_strip<POLICY == kShared>(chunks, rows, worker0, n_workers, w);
     const int q = lane_id();
     if (q >= st.nq) return;
     f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
@@ -831,7 +840,7 @@ constexpr int pass2_waves(int stores) { return stores <= 2 ? 20 : stores == 3 ? 
 constexpr int copy_waves(int n) {
     return n == 1 ? kAllWaves : n == 2 ? 20 : n == 3 ? 16 : n <= 5 ? 12 : 8;
 }
-constexpr int kInitWaves = 12;
+constexpr int init_waves(int n) { return n == 1 ? 16 : 8; }
 
 // A launch that touches less than half the 256 MB last-level cache is over
 // before its rows fight: it is bound by latency, and takes all the waves that
@@ -891,7 +900,7 @@ hipError_t launch_init(const Chunk* chunks, int64_t n_chunks, float* x, float* m
                        float* x_rep, RepLayout rl, float* s1, float* s2, StateLayout ml, int n,
                        int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    launch_strips(k_init, chunks, n_chunks, rl, map, 3 * n + 2, kInitWaves, st, x, m, v, x_rep, rl,
+    launch_strips(k_init, chunks, n_chunks, rl, map, 3 * n + 2, init_waves(n), st, x, m, v, x_rep, rl,
                   s1, s2, ml, n);
     return hipGetLastError();
 }
@@ -909,6 +918,7 @@ static void launch_local(K kernel, const Chunk* chunks, int64_t n_chunks, const 
     // n = 2, 80.5 us against 81.4 us; with full chunks it is the other way
     // round, 75.8 us against 74.4 us for 8 tensors of 128K, n = 4).
     if (small && rl.groups > 0) map = kQuads;
+    if (small) map &= ~kWideTurns;  // 2% of a round of 350K elements, n = 16
     const int group_waves = map & kQuads ? kQuadWaves : 1;
     hipLaunchKernelGGL(kernel, local_grid(n_chunks, rl, n_workers, map), dim3(group_waves * kWave),
                        lds_for(small ? kAllWaves : waves), st, chunks, rows_of(n_chunks, rl, map),
@@ -945,7 +955,7 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
 // worker in the rare launch whose row is too long to interleave).  One wave
 // taking all n steps of a strip, with its 3 n + 1 streams at a time, ran at
 // 66.1% (small, n = 8, state-blocked) and 67.5% (n = 4, contiguous) of 8 TB/s
-// over the same bytes; this at 83.1% and 78.3%.
+// over the same bytes; this at 83.1% and 80%.
 hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const float* x,
                                float* x_rep, RepLayout rl, const float* g_rep, float* s1,
                                float* s2, StateLayout ml, int n, bool adamw,
