@@ -818,8 +818,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_write(float* __restric
 constexpr unsigned lds_for(int groups) {
     return groups >= kAllWaves ? 0u : static_cast<unsigned>(160 * 1024 / groups / 1280 * 1280);
 }
-// The same for work-groups of `waves` waves, at most `per_cu` waves per CU.
-constexpr unsigned lds_for(int per_cu, int waves) { return lds_for((per_cu + waves / 2) / waves); }
+// The same for work-groups of four waves, at most `waves` waves per CU, beside
+// up to 256 bytes of LDS that the kernel itself holds: a step more, and one
+// work-group fewer would fit.
+constexpr unsigned quad_lds(int waves) {
+    return waves >= kAllWaves ? 0u : lds_for((waves + kQuadWaves / 2) / kQuadWaves) - 256;
+}
 
 // Waves per CU by kernel, swept from 6 to 32 at GPT-2 small to xl.  Local
 // steps: AdamW (four loads) 12, SGD (three, and little arithmetic) 20: medium,
@@ -885,7 +889,7 @@ void launch_strips(K kernel, const Chunk* chunks, int64_t n_chunks, const RepLay
     waves = waves_for(n_chunks, rl, streams, waves);
     if (map & kQuads)
         hipLaunchKernelGGL(kernel, quad_grid(n_chunks, rl), dim3(kBlockThreads),
-                           lds_for(waves, kQuadWaves), stream, chunks, rows,
+                           quad_lds(waves), stream, chunks, rows,
                            args...);
     else
         hipLaunchKernelGGL(kernel, strip_grid(n_chunks, rl), dim3(kWave), lds_for(waves), stream,
@@ -995,7 +999,13 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
                                    hipStream_t st) {
     constexpr int strips = PIECE ? kQuadWaves : 1;
     const dim3 grid = PIECE ? quad_grid(n_chunks, a.rl) : strip_grid(n_chunks, a.rl);
-    int workers = a.gs.n < kMaxRoundEndWaves / strips ? a.gs.n : kMaxRoundEndWaves / strips;
+    // AdamW's waves take longer and less evenly than SGD's, and a barrier over
+    // 16 of them waits longer than two shares per wave of 8 do: n = 16, 30M
+    // parameters, AdamW 65.3% (contiguous) and 72.6% (state-blocked) of 8 TB/s
+    // with 16 waves, 68.0% and 75.4% with 8; SGD 73.9% and 83.8%, 70.0% and
+    // 78.9%.
+    constexpr int max_waves = BASE == kBaseSgd || PIECE ? kMaxRoundEndWaves : kMaxRoundEndWaves / 2;
+    int workers = a.gs.n < max_waves / strips ? a.gs.n : max_waves / strips;
     // A grid dimension holds fewer than 2^32 threads.
     while (static_cast<int64_t>(grid.x) * workers * strips * kWave >= (int64_t(1) << 32))
         workers /= 2;
