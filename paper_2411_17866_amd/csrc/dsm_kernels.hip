@@ -810,8 +810,9 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_write(float* __restric
 // Local AdamW, GPT-2 small, n = 4, contiguous (% of 8 TB/s): 4 KiB pieces, an
 // eighth of the arena per XCD, all waves resident 70.6-73.1; 4 KiB pieces in
 // grid order, 12 waves per CU 79.8; 1 KiB strips 76.9 with all waves resident,
-// 79.4 with 16 per CU, 82.7 with 12, below 77 with 8.  State-blocked, n = 8:
-// 75.8 before, 84.6 now.
+// 79.4 with 16 per CU, 82.7 with 12, below 77 with 8.  With 12 waves per CU and
+// the XCDs taking 512 B or 256 B of a stream in turn 77.1 and 64.5, 2 KiB or
+// 4 KiB 79.7 and 80.2.  State-blocked, n = 8: 75.8 before, 84.6 now.
 //
 // Dynamic LDS that lets at most `groups` work-groups live on a CU (its 160 KiB
 // come in steps of 1280 bytes).
@@ -888,9 +889,8 @@ void launch_strips(K kernel, const Chunk* chunks, int64_t n_chunks, const RepLay
     const Rows rows = rows_of(n_chunks, rl, map);
     waves = waves_for(n_chunks, rl, streams, waves);
     if (map & kQuads)
-        hipLaunchKernelGGL(kernel, quad_grid(n_chunks, rl), dim3(kBlockThreads),
-                           quad_lds(waves), stream, chunks, rows,
-                           args...);
+        hipLaunchKernelGGL(kernel, quad_grid(n_chunks, rl), dim3(kBlockThreads), quad_lds(waves),
+                           stream, chunks, rows, args...);
     else
         hipLaunchKernelGGL(kernel, strip_grid(n_chunks, rl), dim3(kWave), lds_for(waves), stream,
                            chunks, rows, args...);
