@@ -52,12 +52,14 @@ struct RepLayout {
     int64_t block_stride;
     int64_t copy_stride;
     int32_t shift;
-    // Of the problem, not of the buffer.  groups: 0, or where most strip groups
-    // of its chunks hold no elements (many tensors far shorter than a chunk),
-    // the number of those that do; its launches then go over these only.
-    // cached: its arenas are small enough to stay in the caches between calls.
-    uint32_t groups : 31;
-    uint32_t cached : 1;
+    // Of the problem, not of the buffer, set by problem_facts().  groups: 0, or
+    // where most strip groups of its chunks hold no elements (many tensors far
+    // shorter than a chunk), the number of those that do; its launches then go
+    // over these only.  cached: its arenas are small enough to stay in the
+    // caches between calls.
+    uint32_t facts;
+    int64_t groups() const { return facts & 0x7fffffffu; }
+    bool cached() const { return facts >> 31 != 0; }
 };
 // Sparse from half the groups empty on.  A wave of a sparse launch searches for
 // its chunk, ~1 us; the waves it saves cost their dispatch (125 tensors of 64K
@@ -70,14 +72,20 @@ constexpr bool sparse_chunks(int64_t groups, int64_t n_chunks) {
 // Three eighths of the 256 MB last-level cache: problems of 106 MB taking turns
 // already lose 2% to plain accesses.
 constexpr int64_t kCachedBytes = int64_t(96) << 20;
+// RepLayout::facts of a problem with `groups` strip groups that hold elements,
+// n_chunks chunks and `bytes` of arenas.
+constexpr uint32_t problem_facts(int64_t groups, int64_t n_chunks, int64_t bytes) {
+    return (sparse_chunks(groups, n_chunks) ? static_cast<uint32_t>(groups) : 0u) |
+           (bytes <= kCachedBytes ? 0x80000000u : 0u);
+}
 // n contiguous copies of d_pad elements.
-inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0, 0}; }
+inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0}; }
 // n copies interleaved in 64 KiB blocks.
 inline RepLayout blocked_copies(int n) {
-    return RepLayout{int64_t(n) * kRepBlockElems, kRepBlockElems, kRepBlockShift, 0, 0};
+    return RepLayout{int64_t(n) * kRepBlockElems, kRepBlockElems, kRepBlockShift, 0};
 }
 // Every copy is the same single buffer (stale replicas read the global x).
-inline RepLayout single_copy() { return RepLayout{0, 0, 62, 0, 0}; }
+inline RepLayout single_copy() { return RepLayout{0, 0, 62, 0}; }
 
 // The replicas and their state in one allocation (dsm_problem.replica_layout =
 // DSM_REPLICAS_STATE_BLOCKED): 16 KiB blocks, and block b holds the n x_rep
@@ -89,7 +97,7 @@ constexpr int64_t kStateBlockElems = int64_t(1) << kStateBlockShift;
 static_assert(kStateBlockElems % kPieceElems == 0, "a state block must hold whole pieces");
 inline RepLayout state_blocked_copies(int n, int buffers) {
     return RepLayout{int64_t(buffers) * n * kStateBlockElems, kStateBlockElems, kStateBlockShift,
-                     0, 0};
+                     0};
 }
 
 // Where the gradient and the base-optimizer moments of worker i keep their
@@ -181,7 +189,7 @@ constexpr XcdMaps kMapsByLayout[3] = {
     {kInterleaveWorkers, 0, kInterleaveWorkers, kQuads, kQuads}};  // state-blocked
 
 // How a kernel finds its strips: the launch map, and the number of chunks when
-// it goes over the strip groups that hold elements (RepLayout::groups), else 0.
+// it goes over the strip groups that hold elements (RepLayout::groups()), else 0.
 struct Rows {
     int32_t map;
     uint32_t sparse_chunks;

@@ -34,7 +34,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // interleaved order the n workers read one soon after the other: a plain load
 // leaves it in the caches for the others, and x comes from HBM once.
 // kCached: plain loads and stores, for problems whose arenas are still in the
-// 256 MB last-level cache at the next call (RepLayout::cached): rounds of 1.1M
+// 256 MB last-level cache at the next call (RepLayout::cached()): rounds of 1.1M
 // elements, n = 2, 27.8 us against 36.6 us with nontemporal ones; 8 x 128K,
 // n = 4 (75 MB), 74.4 us against 84.0 us; but 161 MB 167.9 against 165.2 us and
 // 510 MB 344 against 317 us.
@@ -854,10 +854,10 @@ constexpr int64_t kSmallBytes = int64_t(128) << 20;
 
 // Strip groups of a launch, and the Rows its kernel finds them by.
 int64_t groups_of(int64_t n_chunks, const RepLayout& rl) {
-    return rl.groups > 0 ? rl.groups : n_chunks * (kStrips / kGroupStrips);
+    return rl.groups() > 0 ? rl.groups() : n_chunks * (kStrips / kGroupStrips);
 }
 Rows rows_of(int64_t n_chunks, const RepLayout& rl, int map) {
-    return Rows{map, rl.groups > 0 ? static_cast<uint32_t>(n_chunks) : 0u};
+    return Rows{map, rl.groups() > 0 ? static_cast<uint32_t>(n_chunks) : 0u};
 }
 dim3 strip_grid(int64_t n_chunks, const RepLayout& rl) {
     return dim3(static_cast<unsigned>(groups_of(n_chunks, rl) * kGroupStrips));
@@ -921,7 +921,7 @@ static void launch_local(K kernel, const Chunk* chunks, int64_t n_chunks, const 
     // elements in all, n = 16: round 57 us against 66 us; 400 tensors of 3M,
     // n = 2, 80.5 us against 81.4 us; with full chunks it is the other way
     // round, 75.8 us against 74.4 us for 8 tensors of 128K, n = 4).
-    if (small && rl.groups > 0) map = kQuads;
+    if (small && rl.groups() > 0) map = kQuads;
     if (small) map &= ~kWideTurns;  // 2% of a round of 350K elements, n = 16
     const int group_waves = map & kQuads ? kQuadWaves : 1;
     hipLaunchKernelGGL(kernel, local_grid(n_chunks, rl, n_workers, map), dim3(group_waves * kWave),
@@ -935,7 +935,7 @@ hipError_t launch_local_adamw(const Chunk* chunks, int64_t n_chunks, float* x_re
                               const AdamScalars& sc, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    launch_local(rl.cached ? k_local_adamw<kCached> : k_local_adamw<kStream>, chunks, n_chunks, rl,
+    launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kStream>, chunks, n_chunks, rl,
                  map, 4, kAdamWWaves, n_workers, st, x_rep, rl, x_src, sl, g_rep, s1, s2, ml,
                  worker0, n_workers, sc);
     return hipGetLastError();
@@ -947,7 +947,7 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
                              int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    launch_local(rl.cached ? k_local_sgdm<kCached> : k_local_sgdm<kStream>, chunks, n_chunks, rl,
+    launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kStream>, chunks, n_chunks, rl,
                  map, 3, kSgdWaves, n_workers, st, x_rep, rl, x_src, sl, g_rep, s1, ml, worker0,
                  n_workers, sc);
     return hipGetLastError();
@@ -968,11 +968,11 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n, map);
     if (adamw)
-        launch_local(rl.cached ? k_local_adamw<kCached> : k_local_adamw<kShared>, chunks, n_chunks,
+        launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kShared>, chunks, n_chunks,
                      rl, map, 4, kAdamWSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1,
                      s2, ml, 0, n, as);
     else
-        launch_local(rl.cached ? k_local_sgdm<kCached> : k_local_sgdm<kShared>, chunks, n_chunks,
+        launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kShared>, chunks, n_chunks,
                      rl, map, 3, kSgdSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1, ml,
                      0, n, ss);
     return hipGetLastError();
@@ -1014,7 +1014,7 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
                                          round_end_groups(workers) + (KIND == 2 ? 1 : 0));
     const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
     const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
-    const auto kernel = a.rl.cached ? k_round_end<BASE, KIND, PIECE, kCached>
+    const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
                                     : k_round_end<BASE, KIND, PIECE, kStream>;
     hipLaunchKernelGGL(kernel, grid, dim3(workers * strips * kWave), lds, st, chunks, rows_of(n_chunks, a.rl, a.map), a.x, a.m, a.x_rep, a.rl, a.x_src,
                        a.sl, a.g_rep, a.s1, a.s2, a.u, a.bound.piece_max, a.ml, workers, a.as, a.ss,
@@ -1072,7 +1072,7 @@ static void launch_rand_rest(const Chunk* chunks, int64_t n_chunks, int n_tensor
     if (n_tensors > 0 && !fold)
         hipLaunchKernelGGL(k_bound_reduce, dim3(static_cast<unsigned>(n_tensors)),
                            dim3(kReduceThreads), 0, st, chunks, bw.piece_max, bw.chunk0, bw.bits,
-                           rl.groups > 0);
+                           rl.groups() > 0);
     if (n_chunks == 0) return;
     const int stores = broadcast ? sc.n + 1 : 1;
 #define DSM_PASS2(MODE, B, POLICY, FOLD)                                                        \
@@ -1080,9 +1080,9 @@ static void launch_rand_rest(const Chunk* chunks, int64_t n_chunks, int n_tensor
                   stores + 1, pass2_waves(stores), st, x, x_rep, rl, u, bw, sc)
 #define DSM_PASS2_POLICY(MODE, B)                                                               \
     do {                                                                                        \
-        if (!fold && !rl.cached) DSM_PASS2(MODE, B, kStream, false);                            \
+        if (!fold && !rl.cached()) DSM_PASS2(MODE, B, kStream, false);                            \
         else if (!fold) DSM_PASS2(MODE, B, kCached, false);                                     \
-        else if (!rl.cached) DSM_PASS2(MODE, B, kStream, true);                                 \
+        else if (!rl.cached()) DSM_PASS2(MODE, B, kStream, true);                                 \
         else DSM_PASS2(MODE, B, kCached, true);                                                 \
     } while (0)
     if (sc.mode == 1) {
@@ -1114,7 +1114,7 @@ template <int RULE, bool BCAST>
 static void launch_global_det_n(const Chunk* chunks, int64_t n_chunks, float* x, float* m,
                                 float* v, float* x_rep, RepLayout rl, const GlobalScalars& sc,
                                 int map, hipStream_t st) {
-    if (rl.cached) {
+    if (rl.cached()) {
         launch_strips(k_global_det<0, RULE, BCAST, kCached>, chunks, n_chunks, rl, map, sc.n + 2,
                       global_waves(sc.n), st, x, m, v, x_rep, rl, sc);
         return;
@@ -1175,7 +1175,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
 #define DSM_PASS1(NW, POLICY)                                                                    \
     launch_strips(k_global_rand_pass1<NW, POLICY>, chunks, n_chunks, rl, kQuads, sc.n + 3,       \
                   pass1_waves(sc.n), st, x, m, x_rep, rl, u, bw.piece_max, sc)
-        if (rl.cached)
+        if (rl.cached())
             DSM_PASS1(0, kCached);
         else switch (sc.n) {
             case 1: DSM_PASS1(1, kStream); break;
@@ -1193,7 +1193,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
 hipError_t launch_broadcast(const Chunk* chunks, int64_t n_chunks, const float* x, float* x_rep,
                             RepLayout rl, int n, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    launch_strips(rl.cached ? k_broadcast<kCached> : k_broadcast<kStream>, chunks, n_chunks, rl, map, n + 1, copy_waves(n), st, x, x_rep, rl, n);
+    launch_strips(rl.cached() ? k_broadcast<kCached> : k_broadcast<kStream>, chunks, n_chunks, rl, map, n + 1, copy_waves(n), st, x, x_rep, rl, n);
     return hipGetLastError();
 }
 
