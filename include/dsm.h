@@ -337,7 +337,8 @@ DSM_API dsm_status dsm_test_philox(uint64_t seed, uint32_t tensor, int64_t t, in
  * library's kernels, 16-byte nontemporal loads or stores with consecutive lanes
  * on consecutive 16-byte groups, one piece of DSM_PIECE_ELEMS elements per
  * 256-thread work-group.  It measures the device's pure read and pure write
- * rates, and calibrates byte counters against the library's own accesses.  It is a measurement aid, not a step of the method.
+ * rates, and calibrates byte counters against the library's own accesses.
+ * It is a measurement aid, not a step of the method.
  *   DSM_STREAM_READ:  reads every element; for each piece k whose elements'
  *                     32-bit patterns XOR to `pattern`, writes 1 to
  *                     dev_words[k] (caller-owned, n_elems / DSM_PIECE_ELEMS
