@@ -117,6 +117,21 @@ struct Chunk {
 };
 static_assert(sizeof(Chunk) == 32, "chunk descriptor is 32 bytes");
 
+// One level of the search for the chunk that holds a strip group, over the
+// ascending Chunk.group0: a wave's 64 lanes probe the range at equal steps, and
+// the number of lanes that find a group0 at or below the group (a prefix with
+// lane 0 in it) narrows the range to one step.
+struct ChunkRange {
+    uint32_t lo, size;
+};
+constexpr uint32_t probe_step(const ChunkRange& r) { return (r.size + kWave - 1) / kWave; }
+// Offset into the range that a lane probes; past the range when not below size.
+constexpr uint32_t probe_of(const ChunkRange& r, uint32_t lane) { return lane * probe_step(r); }
+constexpr ChunkRange narrowed(const ChunkRange& r, uint32_t below) {
+    const uint32_t step = probe_step(r), skip = (below - 1) * step;
+    return ChunkRange{r.lo + skip, step < r.size - skip ? step : r.size - skip};
+}
+
 // fp32 coefficients of one AdamW local step, formed on the host in fp64 and
 // rounded once.
 struct AdamScalars {

@@ -109,15 +109,13 @@ __device__ __forceinline__ int wave_id() {
 // strips per search lose 1% (rounds of 17.4 and 78.4 us).
 __device__ __forceinline__ uint32_t find_chunk(const Chunk* __restrict__ chunks, uint32_t n_chunks,
                                                uint32_t g) {
-    uint32_t lo = 0, size = n_chunks;
-    while (size > 1) {
-        const uint32_t step = (size + 63) / 64, at = static_cast<uint32_t>(lane_id()) * step;
-        const bool at_or_below = at < size && chunks[lo + min(at, size - 1)].group0 <= g;
-        const uint32_t k = static_cast<uint32_t>(__popcll(__ballot(at_or_below))) - 1;
-        lo += k * step;
-        size = min(step, size - k * step);
+    ChunkRange r{0, n_chunks};
+    while (r.size > 1) {
+        const uint32_t at = probe_of(r, static_cast<uint32_t>(lane_id()));
+        const bool at_or_below = at < r.size && chunks[r.lo + min(at, r.size - 1)].group0 <= g;
+        r = narrowed(r, static_cast<uint32_t>(__popcll(__ballot(at_or_below))));
     }
-    return __builtin_amdgcn_readfirstlane(lo);
+    return __builtin_amdgcn_readfirstlane(r.lo);
 }
 
 // Strip si of a launch: of all chunks' kStrips each, or (rows.sparse_chunks

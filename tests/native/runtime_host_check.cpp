@@ -13,6 +13,8 @@
 //     (the replica, or x after a global step without broadcast), with the
 //     replica addressing of both replica layouts;
 //   * the fp32 coefficients formed on the host, against long double;
+//   * the facts a launch is dispatched by (strip groups, cached), the chunk table's
+//     group index and the search over it, and the bound words as uploaded;
 //   * error paths: no device, failed launches, bad hyperparameters, NULLs;
 //   * contexts driven from several threads at once (also built with the
 //     thread sanitizer, where `threads` as the only argument runs just that).
@@ -71,6 +73,7 @@ struct Launch {
     const uint32_t* piece_max = nullptr;
     const int32_t* chunk0 = nullptr;
     int worker0 = -1, n_workers = -1, n_tensors = -1;
+    int64_t max_words = -1;
     dsm::StateLayout ml{{-1, -1, -1, 0}, {-1, -1, -1, 0}, {-1, -1, -1, 0}};
     bool broadcast = false, adamw = false;
     dsm::AdamScalars as{};
@@ -206,6 +209,7 @@ hipError_t launch_round_end(const Chunk* chunks, int64_t n_chunks, int n_tensors
     l.bounds = a.bound.bits;
     l.piece_max = a.bound.piece_max;
     l.chunk0 = a.bound.chunk0;
+    l.max_words = a.bound.max_words;
     l.ml = a.ml;
     l.broadcast = broadcast;
     l.as = a.as;
@@ -245,6 +249,7 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
     l.bounds = bw.bits;
     l.piece_max = bw.piece_max;
     l.chunk0 = bw.chunk0;
+    l.max_words = bw.max_words;
     l.gs = sc;
     l.broadcast = broadcast;
     return record(l);
@@ -582,6 +587,134 @@ void check_init_and_chunks() {
                                   reinterpret_cast<const uint32_t*>(ws + po), "init");
             }
             CHECK(dsm_destroy(ctx) == DSM_OK, "destroy");
+        }
+    }
+}
+
+// Strip groups (2048 elements, 8 of a chunk's 16384) that hold elements, the
+// facts that every launch of a problem is dispatched by, and the words of the
+// randomized sign's bound, written out from the sizes alone.
+struct Facts {
+    std::vector<uint32_t> group0;  // of each chunk
+    int64_t groups = 0, n_chunks = 0, max_words = 0;
+    bool sparse = false, cached = false;
+    Facts(const Problem& P, int64_t arena) {
+        for (int64_t ne : P.numel) {
+            max_words = std::max<int64_t>(max_words, (ne + 16383) / 16384 * 16);
+            for (int64_t left = ne; left > 0; left -= 16384, ++n_chunks) {
+                group0.push_back(static_cast<uint32_t>(groups));
+                groups += (std::min<int64_t>(left, 16384) + 2047) / 2048;
+            }
+        }
+        sparse = groups * 2 <= n_chunks * 8;
+        const int64_t per_worker = P.p.base == DSM_BASE_ADAMW ? 4 : 3;
+        cached = (2 + P.p.n_workers * per_worker) * arena * 4 <= 96 * 1024 * 1024;
+    }
+};
+
+// Every launch of P carries its facts, the uploaded table its group index, and
+// the upload zeroes the bounds.
+void check_facts_of(const Problem& P, bool want_sparse, bool want_cached, const char* what) {
+    Buffers B(P, true, false);
+    const Facts f(P, B.arena);
+    CHECK(f.sparse == want_sparse && f.cached == want_cached, "%s: the case is what it claims", what);
+    const bool adamw = P.p.base == DSM_BASE_ADAMW;
+    const dsm_local_hparams lh = adamw ? adam_hp() : sgd_hp();
+    const dsm_global_hparams det = glob_hp(), rnd = glob_hp(DSM_SIGN_RAND_FLIP);
+    g_log.clear();
+    dsm_ctx* ctx = nullptr;
+    CHECK(dsm_init(&P.p, &B.b, &ctx) == DSM_OK, "%s: init: %s", what, dsm_last_error(nullptr));
+    const auto* c = static_cast<const dsm::Chunk*>(B.b.workspace);
+    for (int64_t k = 0; k < f.n_chunks; ++k)
+        CHECK(c[k].group0 == f.group0[k], "%s: chunk %lld group0 %u, expected %u", what,
+              static_cast<long long>(k), c[k].group0, f.group0[k]);
+    const auto* bits = reinterpret_cast<const uint32_t*>(
+        static_cast<const char*>(B.b.workspace) + round_up(f.n_chunks * 32, 256));
+    for (size_t i = 0; i < P.numel.size(); ++i)
+        CHECK(bits[i] == 0, "%s: bound %zu uploaded as 0x%x", what, i, bits[i]);
+    // H = 2: a split randomized round, lazily synchronised, a fused one from x,
+    // a split deterministic one, and the synchronisation.
+    CHECK(dsm_local_step(ctx, -1, 1, &lh) == DSM_OK, "%s: all workers", what);
+    for (int i = 0; i < P.p.n_workers; ++i)
+        CHECK(dsm_local_step(ctx, i, 2, &lh) == DSM_OK, "%s: worker %d", what, i);
+    CHECK(dsm_global_step(ctx, 0, &rnd, 0) == DSM_OK, "%s: randomized step", what);
+    CHECK(dsm_local_step(ctx, -1, 3, &lh) == DSM_OK, "%s: from x", what);
+    CHECK(dsm_round_end(ctx, 4, &lh, 1, &rnd, 1) == DSM_OK, "%s: round end", what);
+    for (int k = 5; k < 7; ++k) CHECK(dsm_local_step(ctx, -1, k, &lh) == DSM_OK, "%s: local", what);
+    CHECK(dsm_global_step(ctx, 2, &det, 1) == DSM_OK, "%s: global step", what);
+    CHECK(dsm_sync(ctx) == DSM_OK, "%s: sync", what);
+    CHECK(g_log.size() == static_cast<size_t>(9 + P.p.n_workers), "%s: %zu launches", what,
+          g_log.size());
+    for (const Launch& l : g_log) {
+        CHECK(l.rl.groups() == (f.sparse ? f.groups : 0), "%s: %s over %lld strip groups, not %lld",
+              what, l.kind.c_str(), static_cast<long long>(l.rl.groups()),
+              static_cast<long long>(f.sparse ? f.groups : 0));
+        CHECK(l.rl.cached() == f.cached, "%s: %s cached %d", what, l.kind.c_str(), l.rl.cached());
+        const bool bound = l.kind == "round_end" || l.kind == "global_rand";
+        CHECK(l.max_words == (bound ? f.max_words : -1), "%s: %s with %lld words at most", what,
+              l.kind.c_str(), static_cast<long long>(l.max_words));
+    }
+    CHECK(dsm_destroy(ctx) == DSM_OK, "%s: destroy", what);
+}
+
+void check_facts() {
+    // On both sides of half-empty groups (8192 elements are 4 groups of a
+    // chunk's 8), and tables with empty tensors, tails and full chunks.
+    for (int layout : {DSM_REPLICAS_CONTIGUOUS, DSM_REPLICAS_BLOCKED, DSM_REPLICAS_STATE_BLOCKED}) {
+        const auto facts = [&](std::vector<int64_t> ne, bool sparse, const char* what) {
+            for (int base : {DSM_BASE_ADAMW, DSM_BASE_SGD_MOMENTUM})
+                check_facts_of(Problem(ne, 2, 2, base, {}, layout), sparse, true, what);
+        };
+        facts({8192}, true, "half the groups");
+        facts({8193}, false, "one element past half");
+        facts({8193, 6144}, true, "half the groups of two chunks");
+        facts({8193, 6145}, false, "one group past half of two chunks");
+        facts({1, 2047, 2048, 2049, 0, 16384, 0, 5, 16385, 40003, 1, 1, 1, 1, 1}, true, "ragged");
+        facts({16384, 32769, 14337, 0, 16383}, false, "full chunks");
+    }
+    // On both sides of 96 MiB of arenas: 5 copies of one worker's SGD, 10 of
+    // two workers' AdamW.
+    for (int64_t past : {0, 1}) {
+        check_facts_of(Problem({5033152 + past}, 1, 2, DSM_BASE_SGD_MOMENTUM), false, past == 0,
+                       "SGD, 96 MiB");
+        check_facts_of(Problem({2516544 + past}, 2, 2, DSM_BASE_ADAMW), false, past == 0,
+                       "AdamW, 96 MiB");
+    }
+}
+
+// The 64-ary search of a sparse launch, lane by lane, against a linear scan:
+// every strip group of tables with one to four levels.
+void check_chunk_search() {
+    std::mt19937_64 rng(99);
+    for (uint32_t n : {1u, 2u, 63u, 64u, 65u, 127u, 4095u, 4096u, 4097u, 8200u, 262145u}) {
+        std::vector<uint32_t> group0(n);
+        uint32_t total = 0;
+        for (uint32_t k = 0; k < n; ++k) {
+            group0[k] = total;
+            total += 1 + static_cast<uint32_t>(rng() % 8);
+        }
+        // Every group of the small tables, the first and last of each chunk of
+        // the others' ends, and a sample.
+        for (uint32_t want = 0; want < n; ++want) {
+            if (n > 8200 && want > 200 && want < n - 200 && rng() % 100 != 0) continue;
+            const uint32_t last = want + 1 < n ? group0[want + 1] - 1 : total - 1;
+            for (uint32_t g : {group0[want], last}) {
+                dsm::ChunkRange r{0, n};
+                while (r.size > 1) {
+                    uint32_t below = 0;
+                    for (uint32_t lane = 0; lane < 64; ++lane) {
+                        const uint32_t at = dsm::probe_of(r, lane);
+                        if (at < r.size && group0[r.lo + at] <= g) ++below;
+                    }
+                    CHECK(below >= 1 && below <= 64, "lane 0 always counts");
+                    const dsm::ChunkRange next = dsm::narrowed(r, below);
+                    CHECK(next.size < r.size && next.size >= 1 && next.lo + next.size <= n,
+                          "%u chunks: range [%u, +%u)", n, next.lo, next.size);
+                    if (next.size >= r.size || next.size == 0) return;
+                    r = next;
+                }
+                CHECK(r.lo == want, "%u chunks, group %u: chunk %u, expected %u", n, g, r.lo, want);
+            }
         }
     }
 }
@@ -1319,6 +1452,8 @@ int main(int argc, char** argv) {
     check_local_map();
     check_layout_fuzz();
     check_init_and_chunks();
+    check_facts();
+    check_chunk_search();
     check_init_rejections();
     check_init_static();
     check_blocked_addressing(DSM_REPLICAS_BLOCKED);

@@ -85,6 +85,19 @@ MUTATIONS = [
     ("ctx->bound.piece_max = reinterpret_cast<uint32_t*>(ws + L.piece_max_off);",
      "ctx->bound.piece_max = reinterpret_cast<uint32_t*>(ws + L.chunk0_off);",
      "piece maxima over the tensor chunk index"),
+    ("c.group0 = static_cast<uint32_t>(L->groups);", "c.group0 = 0;",
+     "chunk table without its strip-group index"),
+    ("L->groups += (c.len + dsm::kGroupElems - 1) / dsm::kGroupElems;",
+     "L->groups += c.len / dsm::kGroupElems;", "strip groups of a chunk rounded down"),
+    ("int64_t(ctx->chunk0[i + 1] - ctx->chunk0[i]) * dsm::kSplit);",
+     "int64_t(ctx->chunk0[i + 1] - ctx->chunk0[i]) * 0);", "no bound words counted"),
+    ("dsm::problem_facts(L.groups, L.n_chunks, 4 * copies * L.arena_elems);",
+     "dsm::problem_facts(L.groups, L.n_chunks, copies);", "every problem counted as cached"),
+    ("dsm::problem_facts(L.groups, L.n_chunks, 4 * copies * L.arena_elems);",
+     "dsm::problem_facts(L.groups - 1, L.n_chunks, 4 * copies * L.arena_elems);",
+     "one strip group too few"),
+    ("(L.chunk0_off - L.bounds_off) / sizeof(int32_t), 0);",
+     "(L.chunk0_off - L.bounds_off) / sizeof(int32_t), 7);", "bounds uploaded as 7"),
     ("    if (n_pieces * dsm::kBlockThreads >= (int64_t(1) << 32))",
      "    if (n_pieces * dsm::kBlockThreads >= (int64_t(1) << 40))",
      "streaming diagnostic grid past one dimension"),
