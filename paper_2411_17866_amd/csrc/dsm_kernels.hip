@@ -816,34 +816,54 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_write(float* __restric
 // the XCDs taking 512 B or 256 B of a stream in turn 77.1 and 64.5, 2 KiB or
 // 4 KiB 79.7 and 80.2.  State-blocked, n = 8: 75.8 before, 84.6 now.
 //
-// Dynamic LDS that lets at most `groups` work-groups live on a CU (its 160 KiB
-// come in steps of 1280 bytes).
+// Dynamic LDS that lets `groups` work-groups live on a CU.  A CU's 160 KiB come
+// in steps of 1280 bytes, so not every count can be had: asked for 13, 19 or 20,
+// 14 and 21 (twice) fit.
+constexpr unsigned kLdsBytes = 160 * 1024, kLdsStep = 1280;
 constexpr unsigned lds_for(int groups) {
-    return groups >= kAllWaves ? 0u : static_cast<unsigned>(160 * 1024 / groups / 1280 * 1280);
+    return groups >= kAllWaves ? 0u : kLdsBytes / static_cast<unsigned>(groups) / kLdsStep * kLdsStep;
 }
-// The same for work-groups of four waves, at most `waves` waves per CU, beside
-// up to 256 bytes of LDS that the kernel itself holds: a step more, and one
-// work-group fewer would fit.
+// Work-groups that fit a CU with that much LDS each.
+constexpr int groups_with(unsigned lds) {
+    return lds == 0 ? kAllWaves : static_cast<int>(kLdsBytes / ((lds + kLdsStep - 1) / kLdsStep * kLdsStep));
+}
+constexpr bool attainable(int groups) { return groups_with(lds_for(groups)) == groups; }
+// The same for work-groups of four waves, the whole number of them nearest to
+// `waves` waves per CU (10 gives 12), beside up to 256 bytes of LDS that the
+// kernel itself holds: a step more, and one work-group fewer would fit.
 constexpr unsigned quad_lds(int waves) {
     return waves >= kAllWaves ? 0u : lds_for((waves + kQuadWaves / 2) / kQuadWaves) - 256;
 }
+static_assert(groups_with(quad_lds(8)) == 2 && groups_with(quad_lds(10)) == 3 &&
+                  groups_with(quad_lds(12)) == 3 && groups_with(quad_lds(16)) == 4 &&
+                  groups_with(quad_lds(20)) == 5,
+              "work-groups of four waves");
 
 // Waves per CU by kernel, swept from 6 to 32 at GPT-2 small to xl.  Local
-// steps: AdamW (four loads) 12, SGD (three, and little arithmetic) 20: medium,
+// steps: AdamW (four loads) 12, SGD (three, and little arithmetic) 21: medium,
 // n = 8, 84.0% against 83.2% with 16 and 78% with 14.  From the shared x one
 // load of most waves hits the L2, so a few more.
 constexpr int kAdamWWaves = 12, kAdamWSharedWaves = 14;
-constexpr int kSgdWaves = 20, kSgdSharedWaves = 18;
+constexpr int kSgdWaves = 21, kSgdSharedWaves = 18;
+static_assert(attainable(kAdamWWaves) && attainable(kAdamWSharedWaves) && attainable(kSgdWaves) &&
+                  attainable(kSgdSharedWaves),
+              "waves of the local steps");
 // The global step loads n + 2 streams at once: n = 4, 80.3% with 8, 77% with
-// 12; n = 1, 81.0% with 12, 76% with 8.
+// 12; n = 1, 81.0% with 12, 76% with 8.  n = 2 has 10 in one-wave work-groups
+// and 12 in those of four.
 constexpr int global_waves(int n) { return n == 1 ? 12 : n == 2 ? 10 : 8; }
+static_assert(attainable(global_waves(1)) && attainable(global_waves(2)) && attainable(global_waves(3)),
+              "waves of the global step");
 // The randomized first pass has no replica to write and lasts well with a few
 // more: n = 4 and 8, 80.7-81.8% with 12; n = 1 and 2, 79.6 and 83.3% with 16.
 constexpr int pass1_waves(int n) { return n <= 2 ? 16 : 12; }
 // The second pass and the synchronisation load two streams and one; their
-// stores count: with one worker 20 and all of them (sync, n = 1: 81.5%, 71%
-// with 12), down to 12 and 8 with many (sync, n = 8: 82-86%, 74% with 32).
-constexpr int pass2_waves(int stores) { return stores <= 2 ? 20 : stores == 3 ? 16 : 12; }
+// stores count: with one worker 21 (20 in work-groups of four) and all of them
+// (sync, n = 1: 81.5%, 71% with 12), down to 12 and 8 with many (sync, n = 8:
+// 82-86%, 74% with 32).
+constexpr int pass2_waves(int stores) { return stores <= 2 ? 21 : stores == 3 ? 16 : 12; }
+static_assert(attainable(pass2_waves(2)) && attainable(pass2_waves(3)) && attainable(pass2_waves(4)),
+              "waves of the second pass");
 constexpr int copy_waves(int n) {
     return n == 1 ? kAllWaves : n == 2 ? 20 : n == 3 ? 16 : n <= 5 ? 12 : 8;
 }
@@ -983,10 +1003,20 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
 // Work-groups of the round end per CU, by waves per work-group.  Many waves
 // of a group wait for its last, so more waves are resident than in a local
 // step, and fewer groups the larger they are (swept 2 to 24 at GPT-2 small to
-// xl; with one worker 77.4% with 10-12, 72% with 8, 74% with 14).
-constexpr int round_end_groups(int waves) {
-    return waves == 1 ? 12 : waves == 2 ? 8 : waves == 3 ? 6 : waves == 4 ? 5 : 4;
+// xl; deterministic, one worker 77.4% with 10-12, 72% with 8, 74% with 14).  The
+// randomized one has one more, or two with one worker.  From eight waves a group on,
+// the 32 waves that a CU holds are the limit: four groups of eight, two of sixteen.
+constexpr int round_end_groups(int waves, bool randomized) {
+    const int groups = waves == 1 ? 12 : waves == 2 ? 8 : waves == 3 ? 6 : waves == 4 ? 5 : 4;
+    return groups + (randomized ? (waves == 1 ? 2 : 1) : 0);
 }
+constexpr bool round_end_groups_attainable() {
+    for (int waves = 1; waves <= kMaxRoundEndWaves; ++waves)
+        if (!attainable(round_end_groups(waves, false)) || !attainable(round_end_groups(waves, true)))
+            return false;
+    return true;
+}
+static_assert(round_end_groups_attainable(), "work-groups of the round end");
 
 // From here on the randomized round end clears the bound words and raises them
 // by atomic maxima, one strip per work-group; below, a work-group takes all
@@ -1013,7 +1043,7 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
         workers /= 2;
     const int groups = PIECE ? kAllWaves
                              : waves_for(n_chunks, a.rl, 4 * a.gs.n + 2,
-                                         round_end_groups(workers) + (KIND == 2 ? 1 : 0));
+                                         round_end_groups(workers, KIND == 2));
     const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
     const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
     const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
