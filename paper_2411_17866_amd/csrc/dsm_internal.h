@@ -165,7 +165,8 @@ struct GlobalScalars {
     float eta, eps;
 };
 
-// How a launch goes over the strips, by kernel kind and replica layout.
+// How a launch goes over the strips (its map), by kernel kind and replica
+// layout.
 // Without flags, one-wave work-groups take the strips in order.
 //
 // kInterleaveWorkers (local steps): the grid is one row of strips x workers in
@@ -190,18 +191,19 @@ struct GlobalScalars {
 // against 78.4%; sync 82-88% in all layouts, 79-81% with one wave), behind
 // elsewhere (global step, contiguous, n = 4: 78.0% against 78.7%).
 // global: the global steps and the randomized second pass of the round end;
-// copy: the broadcast of dsm_sync and the initial copy of dsm_init.
+// copy: the broadcast of dsm_sync and the initial copy of dsm_init.  The round
+// end has shapes of its own.
 constexpr int kInterleaveWorkers = 4;
 constexpr int kQuads = 8;
 constexpr int kWideTurns = 16;
 constexpr uint32_t kTurnGroups = 1024;
-struct XcdMaps {
-    int local, round_end, from_x, global, copy;
+struct LaunchMaps {
+    int local, from_x, global, copy;
 };
-constexpr XcdMaps kMapsByLayout[3] = {
-    {0, 0, kInterleaveWorkers | kWideTurns, 0, kQuads},            // contiguous
-    {0, 0, kInterleaveWorkers | kWideTurns, 0, kQuads},            // blocked
-    {kInterleaveWorkers, 0, kInterleaveWorkers, kQuads, kQuads}};  // state-blocked
+constexpr LaunchMaps kMapsByLayout[3] = {
+    {0, kInterleaveWorkers | kWideTurns, 0, kQuads},            // contiguous
+    {0, kInterleaveWorkers | kWideTurns, 0, kQuads},            // blocked
+    {kInterleaveWorkers, kInterleaveWorkers, kQuads, kQuads}};  // state-blocked
 
 // How a kernel finds its strips: the launch map, and the number of chunks when
 // it goes over the strip groups that hold elements (RepLayout::groups()), else 0.
@@ -222,7 +224,7 @@ inline int local_map(int64_t n_chunks, int n_workers, int map) {
 
 // Kernel launchers (dsm_kernels.hip).  All return the launch status.  The
 // replica buffer x_rep is addressed through its RepLayout rl, and g_rep, s1
-// and s2 through the layouts of ml; map is the launch's XCD map.
+// and s2 through the layouts of ml; map is the launch's map.
 hipError_t launch_init(const Chunk* chunks, int64_t n_chunks, float* x, float* m, float* v,
                        float* x_rep, RepLayout rl, float* s1, float* s2, StateLayout ml, int n,
                        int map, hipStream_t st);
@@ -268,8 +270,7 @@ struct RoundEndArgs {
     AdamScalars as;
     SgdScalars ss;
     GlobalScalars gs;
-    int map;        // XCD map of the round-end kernel
-    int map_pass2;  // and of the randomized sign's second pass
+    int map_pass2;  // launch map of the randomized sign's second pass
 };
 hipError_t launch_round_end(const Chunk* chunks, int64_t n_chunks, int n_tensors, bool adamw,
                             const RoundEndArgs& a, bool broadcast, hipStream_t st);

@@ -1049,7 +1049,7 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
     const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
                                     : k_round_end<BASE, KIND, PIECE, kStream>;
     hipLaunchKernelGGL(kernel, grid, dim3(workers * strips * kWave), lds, st, chunks,
-                       rows_of(n_chunks, a.rl, a.map), a.x, a.m, a.x_rep, a.rl, a.x_src, a.sl,
+                       rows_of(n_chunks, a.rl, 0), a.x, a.m, a.x_rep, a.rl, a.x_src, a.sl,
                        a.g_rep, a.s1, a.s2, a.u, a.bound.piece_max, a.ml, workers, a.as, a.ss,
                        a.gs);
 }

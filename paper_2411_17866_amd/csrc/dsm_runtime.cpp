@@ -24,7 +24,7 @@ struct dsm_ctx {
     std::vector<dsm::Chunk> chunks;  // host copy; the device copy lives in the workspace
     dsm::RepLayout rep{};            // how x_rep holds the n replicas
     dsm::StateLayout ml{};           // how g_rep, s1_rep and s2_rep hold theirs
-    dsm::XcdMaps maps{};             // XCD map of each kernel kind for this layout
+    dsm::LaunchMaps maps{};          // launch map of each kernel kind for this layout
     std::vector<int32_t> chunk0;     // host copy of the workspace's words from the bounds to the
                                      // end of the tensor chunk index
     dsm_buffers buf{};
@@ -636,7 +636,6 @@ dsm_status dsm_round_end(dsm_ctx* ctx, int64_t step, const dsm_local_hparams* lo
     a.u = ctx->buf.u_scratch;
     a.bound = ctx->bound;
     a.ml = ctx->ml;
-    a.map = ctx->maps.round_end;
     a.map_pass2 = ctx->maps.global;
     a.as = lc.adam;
     a.ss = lc.sgd;

@@ -193,7 +193,6 @@ hipError_t launch_round_end(const Chunk* chunks, int64_t n_chunks, int n_tensors
                             const RoundEndArgs& a, bool broadcast, hipStream_t) {
     Launch l;
     l.kind = "round_end";
-    l.map = a.map;
     l.map2 = a.map_pass2;
     l.chunks = chunks;
     l.n_chunks = n_chunks;
@@ -357,7 +356,7 @@ struct Buffers {
     int64_t arena = 0;
     dsm::RepLayout rep{};  // the replica layout every launch must pass
     dsm::RepLayout state{};  // and the layout of g_rep, s1_rep and s2_rep
-    dsm::XcdMaps maps{};     // the XCD maps of the problem's layout
+    dsm::LaunchMaps maps{};  // the launch maps of the problem's layout
     float* alloc(int64_t floats) {
         const size_t bytes = static_cast<size_t>(round_up(std::max<int64_t>(floats, 1) * 4, 256));
         void* p = std::aligned_alloc(256, bytes);
@@ -831,7 +830,7 @@ void check_state_machine_adamw(int layout) {
         CHECK(l.kind == "round_end" && l.adamw && l.broadcast && l.n_tensors == 3, "round end");
         CHECK(l.x_src == B.b.x_rep && same_layout(l.sl, B.rep) && same_layout(l.rl, B.rep),
               "round end reads the replicas");
-        CHECK(l.map == B.maps.round_end && l.map2 == B.maps.global, "round end XCD maps");
+        CHECK(l.map2 == B.maps.global, "launch map of the round end's second pass");
         CHECK(l.u == B.b.u_scratch && l.s2 == B.b.s2_rep, "round end buffers");
         check_bound_words(P, B, l.bounds, l.chunk0, l.piece_max, "round end");
         CHECK(l.gs.mode == DSM_SIGN_RAND_FLIP && l.gs.t == 1 && l.gs.key0 == 0x89ABCDEFu &&

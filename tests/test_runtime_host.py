@@ -14,7 +14,7 @@ the whole C ABI runs without a GPU.  Its checks are:
   * the facts every launch is dispatched by (strip groups that hold elements,
     whether the arenas stay in the caches), the chunk table's group index and
     the search over it;
-  * the Algorithm 1 state machine, with the layouts and XCD map of each launch;
+  * the Algorithm 1 state machine, with the layouts and map of each launch;
   * the replica source of each local launch, fresh or stale;
   * dsm_init_static: the static scratch, its limit, one context per device;
   * the fp32 host coefficients against long double;

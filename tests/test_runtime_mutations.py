@@ -42,9 +42,9 @@ MUTATIONS = [
     ("    a.sl = from_x ? dsm::single_copy() : ctx->rep;", "    a.sl = ctx->rep;",
      "round end after a lazy broadcast reads the stale replicas"),
     ("    ctx->maps = dsm::kMapsByLayout[problem->replica_layout];",
-     "    ctx->maps = dsm::kMapsByLayout[0];", "XCD maps of the contiguous layout for every layout"),
-    ("    a.map_pass2 = ctx->maps.global;", "    a.map_pass2 = ctx->maps.round_end;",
-     "randomized second pass launched with the round-end map"),
+     "    ctx->maps = dsm::kMapsByLayout[0];", "launch maps of the contiguous layout for every layout"),
+    ("    a.map_pass2 = ctx->maps.global;", "    a.map_pass2 = ctx->maps.local;",
+     "randomized second pass launched with the local-step map"),
     ("ctx->base == DSM_BASE_ADAMW, lc.adam, lc.sgd, ctx->maps.from_x, ctx->stream);",
      "ctx->base == DSM_BASE_ADAMW, lc.adam, lc.sgd, ctx->maps.local, ctx->stream);",
      "step from x launched with the local-step map"),
