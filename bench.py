@@ -490,9 +490,9 @@ def main():
     torch.cuda.synchronize()
     dsm.dsm_destroy(ctx2)
 
-    # Practical ceiling of this device over 4 GiB buffers: torch's copy and
-    # fill, and the library's pure-read and pure-write stream kernels (the
-    # optimizer kernels' access shape without their arithmetic).  The read
+    # Pure streams on this device over 4 GiB buffers: torch's copy and fill,
+    # and the library's pure-read and pure-write stream kernels (the optimizer
+    # kernels' 16-byte accesses in a shape of their own).  The read
     # kernel writes a word only for a piece whose XOR matches its pattern; a
     # piece of equal floats XORs to 0, so a non-zero pattern keeps the read
     # free of writes.

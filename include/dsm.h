@@ -335,9 +335,11 @@ DSM_API dsm_status dsm_test_philox(uint64_t seed, uint32_t tensor, int64_t t, in
  * dsm_test_stream - diagnostic: streams n_elems fp32 elements of the device
  * buffer dev_buf (caller-owned, 256-byte aligned) with the accesses of the
  * library's kernels, 16-byte nontemporal loads or stores with consecutive lanes
- * on consecutive 16-byte groups, one piece of DSM_PIECE_ELEMS elements per
- * 256-thread work-group.  It measures the device's pure read and pure write
- * rates, and calibrates byte counters against the library's own accesses.
+ * on consecutive 16-byte groups, in a shape of its own: one piece of
+ * DSM_PIECE_ELEMS elements per 256-thread work-group, an eighth of the buffer
+ * per XCD.  It measures pure read and pure write rates of the device, a
+ * yardstick and not an upper bound, and calibrates byte counters against the
+ * library's own accesses.
  * It is a measurement aid, not a step of the method.
  *   DSM_STREAM_READ:  reads every element; for each piece k whose elements'
  *                     32-bit patterns XOR to `pattern`, writes 1 to
@@ -348,8 +350,7 @@ DSM_API dsm_status dsm_test_philox(uint64_t seed, uint32_t tensor, int64_t t, in
  *                     every element (dev_words unused).
  * Enqueued on `stream`.  Errors: DSM_ERR_INVALID_ARG (unknown kind, n_elems
  * not a non-negative multiple of DSM_PIECE_ELEMS or beyond one grid
- * dimension, NULL or misaligned buffers); DSM_ERR_UNSUPPORTED (a build whose
- * work-group shape knobs give another piece size); DSM_ERR_HIP.
+ * dimension, NULL or misaligned buffers); DSM_ERR_HIP.
  */
 #define DSM_PIECE_ELEMS 1024
 typedef enum dsm_stream_kind { DSM_STREAM_READ = 0, DSM_STREAM_WRITE = 1 } dsm_stream_kind;

@@ -752,9 +752,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_test_philox(uint32_t key0, ui
     out[4 * b + 3] = w3;
 }
 
-// Streaming diagnostics with the access shape of the kernels above: one
+// Streaming diagnostics with the 16-byte nontemporal accesses of the kernels
+// above, consecutive lanes on consecutive groups, in a shape of their own: one
 // piece of kPieceVec float4 groups per work-group, XCD k on the k-th eighth of
-// the buffer, 16-byte nontemporal accesses, consecutive lanes on consecutive groups.  The read
+// the buffer, every wave resident.  The rates are a yardstick, not an upper
+// bound of the kernels' shape.  The read
 // kernel folds its piece into one word (the XOR of its 32-bit patterns) and
 // writes only where that word equals `pattern`, so with a pattern no piece
 // matches it issues no write at all: even one 4-byte store per piece,
