@@ -21,8 +21,9 @@ constexpr int kStrips = kChunkElems / 4 / kStripVec;  // strips per chunk
 constexpr int kGroupStrips = kXcds;
 constexpr int kGroupElems = 4 * kStripVec * kGroupStrips;
 static_assert(kChunkElems % kGroupElems == 0, "a chunk must split into whole strip groups");
-// Work-groups of four waves (quads), and the 1024-element pieces of a chunk,
-// each with one word of the randomized sign's bound.
+// Work-groups of four waves (quads), and the 1024-element pieces of a chunk.
+// The randomized sign's bound has as many words as a chunk has pieces, one for
+// each four strips.
 constexpr int kQuadWaves = 4;
 constexpr int kBlockThreads = kQuadWaves * kWave;
 constexpr int kPieceVec = kBlockThreads;
@@ -249,10 +250,14 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
                                hipStream_t st);
 
 // Workspace words of the randomized sign's per-tensor bound B_p = max |u|,
-// reduced in two levels without atomics.
+// reduced in two levels.  A level-one word is the largest |u| of four strips of
+// one chunk: stored by the work-group that takes the four (strips 8 apart, or
+// four in a row over sparse chunks), or raised by atomic maxima of the four
+// strips of a 1024-element piece (a large round end).  Which four share a word
+// does not matter: level two takes all words of a tensor.
 struct BoundWords {
     uint32_t* bits;         // [n_tensors] B_p, fp32 bit patterns
-    uint32_t* piece_max;    // [n_chunks * kSplit] level one: max |u| of each piece
+    uint32_t* piece_max;    // [n_chunks * kSplit] level one: max |u| of four strips each
     const int32_t* chunk0;  // [n_tensors + 1] first chunk of each tensor; last = n_chunks
     int64_t max_words;      // most level-one words of a tensor
 };

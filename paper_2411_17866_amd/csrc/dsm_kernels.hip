@@ -3,8 +3,9 @@
 //
 // Every kernel streams fp32 arenas: a wave takes one strip (64 lanes x one
 // float4 = 256 elements, 1 KiB per stream) of one chunk of one tensor, with
-// 128-bit nontemporal loads and stores, consecutive lanes on consecutive
-// 16-byte groups, and every element is read and written once per pass.
+// 128-bit loads and stores, nontemporal where nothing reads the line again soon
+// (Policy, below), consecutive lanes on consecutive 16-byte groups, and every
+// element is read and written once per pass.
 // Nothing here is a dense contraction, so there is no MFMA; the bound is HBM
 // bandwidth, and what is left to gain is how close the mix of read and write
 // streams comes to it (see "Launch shape" below).
