@@ -6,7 +6,10 @@ and a chunk (16384); chunk tables whose groups mostly hold nothing (many
 tensors far shorter than a chunk; one, two and three levels of the search over
 64 chunks each); worker counts up to one, on and past a work-group's 16 waves.
 Every value is compared bit for bit: the kernels and the oracle's fp32 mode
-round every written operation alike.
+round every written operation alike.  Mid-size problems, past the caches and
+past small launches, are too much for the oracle: there the fused rounds of all
+workers are compared with per-worker split calls, which go over the strips in
+other orders.
 """
 import numpy as np
 import pytest
@@ -138,3 +141,62 @@ def test_large_randomized_round_end_equals_split(layout):
         del ar
     for name, a, b in zip(("x", "m", "replica", "bounds"), *got):
         same_bits(b, a, name)
+
+
+SPARSE_MID = [(k * 7919) % 9_973 + 1 for k in range(400)] + [1_000_003]    # 3M elements
+SPARSE_LARGE = [(k * 2741) % 4095 + 2 for k in range(16_000)]              # 33M
+DENSE_MID = [20_000_003, 5, 16_385]     # strip groups: 9 whole turns of 1024 and a part
+
+
+@pytest.mark.parametrize("numel,n,base,mode,layout", [
+    (SPARSE_MID, 2, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_FLIP, 2),
+    (SPARSE_MID, 6, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 1),
+    (SPARSE_LARGE, 3, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0),
+    (SPARSE_LARGE, 3, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 2),
+    (DENSE_MID, 6, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0),
+    (DENSE_MID, 3, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 1),
+])
+def test_mid_size_rounds_equal_per_worker_split_calls(numel, n, base, mode, layout):
+    """Two lazy rounds of H = 2 by all-worker local steps and fused round ends
+    against the same rounds by one local step call per worker and global steps
+    with broadcast."""
+    buffers = 4 if base == dsm.DSM_BASE_ADAMW else 3
+    assert 4 * sum(numel) * (2 + buffers * n) > 96 << 20    # nontemporal kernels
+    H, local, got = 2, LOCAL[base], []
+    for fused in (True, False):
+        ar = A.Arenas(numel, n, H, base, replica_layout=LAYOUTS[layout])
+        gen = torch.Generator(device="cuda").manual_seed(8)
+        ar.x.normal_(0.0, 0.02, generator=gen)
+        ar.init()
+        bounds = []
+        for t in range(2):
+            for k in range(H):
+                s = t * H + k + 1
+                for i in range(n):
+                    ar.g_rep[i].normal_(0.0, 0.01 * 0.1 ** t, generator=gen)
+                if fused and k == H - 1:
+                    dsm.dsm_round_end(ar.ctx, s, local, t, gamma=local["lr"], mode=mode, seed=9,
+                                      broadcast=False, **GLOB)
+                elif fused:
+                    dsm.dsm_local_step(ar.ctx, -1, s, **local)
+                else:
+                    for i in range(n):
+                        dsm.dsm_local_step(ar.ctx, i, s, **local)
+            if not fused:
+                dsm.dsm_global_step(ar.ctx, t, gamma=local["lr"], mode=mode, seed=9,
+                                    broadcast=True, **GLOB)
+            if mode != dsm.DSM_SIGN_DET:
+                bounds.append(dsm.dsm_read_bounds(ar.ctx, len(numel)))
+        dsm.dsm_sync(ar.ctx)
+        out = {"x": ar.x, "m": ar.m}
+        for name in ("s1_rep", "s2_rep", "x_rep"):
+            if getattr(ar, name) is not None:
+                out.update({f"{name} {i}": ar.worker(name, i) for i in range(n)})
+        got.append(({k: v.view(torch.int32).clone() for k, v in out.items()}, bounds))
+        ar.destroy()
+        del ar, out
+    (a, bounds_a), (b, bounds_b) = got
+    for name in a:
+        assert torch.equal(a[name], b[name]), name
+    for x, y in zip(bounds_a, bounds_b):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
