@@ -32,6 +32,24 @@ constexpr int kGroupPieces = kGroupStrips / kQuadWaves;
 static_assert(kSplit % kXcds == 0, "the strips of a quad must lie in one chunk");
 // Most waves of a work-group of the fused round end (more workers share them).
 constexpr int kMaxRoundEndWaves = 16;
+// Waves for n workers where at most `most` fit: no more than it takes for the
+// same number of turns, so that the last turn is as full as can be.
+constexpr int even_waves(int n, int most) {
+    const int turns = (n + most - 1) / most;
+    return (n + turns - 1) / turns;
+}
+// Waves a strip of the round end that takes four strips in a work-group.  SGD:
+// 4.  AdamW's waves take longer and less evenly, and a barrier over 16 of them
+// waits longer than more turns of 12 do: 25M elements of all workers,
+// contiguous, randomized round end with its second pass, 4 workers 152 us with
+// 16 waves, 122 us with 8; 7 workers 136 us, 116 us with 12; 8 workers 122 us,
+// 112 us.  Past 15 workers 3 waves would take six turns against four, and 3M
+// elements of 16 workers 19.7 us against 19.2 us (state-blocked 20.1 and 18.2
+// us).  Even turns: 5 AdamW workers 169 us with 4 waves of which one takes two,
+// 120 us with 3; 9 SGD workers 79 us and 76 us.
+constexpr int quad_strip_waves(int n, bool adamw) {
+    return even_waves(n, adamw && n < kMaxRoundEndWaves ? 3 : 4);
+}
 // Arena alignment of every tensor, in elements (256 bytes).
 constexpr int64_t kTensorAlign = 64;
 constexpr int kMaxWorkers = 64;

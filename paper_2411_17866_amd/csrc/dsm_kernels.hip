@@ -1039,8 +1039,9 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
     // parameters, AdamW 65.3% (contiguous) and 72.6% (state-blocked) of 8 TB/s
     // with 16 waves, 68.0% and 75.4% with 8; SGD 73.9% and 83.8%, 70.0% and
     // 78.9%.
-    constexpr int max_waves = BASE == kBaseSgd || PIECE ? kMaxRoundEndWaves : kMaxRoundEndWaves / 2;
-    int workers = a.gs.n < max_waves / strips ? a.gs.n : max_waves / strips;
+    constexpr int max_waves = BASE == kBaseSgd ? kMaxRoundEndWaves : kMaxRoundEndWaves / 2;
+    int workers = PIECE ? quad_strip_waves(a.gs.n, BASE == kBaseAdamW)
+                        : (a.gs.n < max_waves ? a.gs.n : max_waves);
     // A grid dimension holds fewer than 2^32 threads.
     while (static_cast<int64_t>(grid.x) * workers * strips * kWave >= (int64_t(1) << 32))
         workers /= 2;

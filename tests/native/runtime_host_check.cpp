@@ -15,6 +15,7 @@
 //   * the fp32 coefficients formed on the host, against long double;
 //   * the facts a launch is dispatched by (strip groups, cached), the chunk table's
 //     group index and the search over it, and the bound words as uploaded;
+//   * how the round end's workers are shared over waves;
 //   * error paths: no device, failed launches, bad hyperparameters, NULLs;
 //   * contexts driven from several threads at once (also built with the
 //     thread sanitizer, where `threads` as the only argument runs just that).
@@ -679,6 +680,31 @@ void check_facts() {
         check_facts_of(Problem({2516544 + past}, 2, 2, DSM_BASE_ADAMW), false, past == 0,
                        "AdamW, 96 MiB");
     }
+}
+
+// Workers shared over the waves of a round end's work-group: enough waves for
+// every worker, none idle in every turn, no more turns than the most waves need,
+// and at most 16 waves in a work-group of four strips.
+void check_round_end_waves() {
+    for (int n = 1; n <= 64; ++n) {
+        for (int most : {3, 4, 8, 16}) {
+            const int waves = dsm::even_waves(n, most), turns = (n + most - 1) / most;
+            CHECK(waves >= 1 && waves <= most && waves <= n, "%d workers: %d of %d waves", n, waves,
+                  most);
+            CHECK((n + waves - 1) / waves == turns, "%d workers on %d waves: turns", n, waves);
+            CHECK(waves == 1 || (n + waves - 2) / (waves - 1) > turns,
+                  "%d workers: %d waves would do", n, waves - 1);
+        }
+        for (bool adamw : {false, true})
+            if (n <= dsm::kMaxRoundEndWaves)
+                CHECK(dsm::quad_strip_waves(n, adamw) * dsm::kQuadWaves <= dsm::kMaxRoundEndWaves,
+                      "%d workers: a work-group holds 16 waves", n);
+    }
+    CHECK(dsm::quad_strip_waves(4, true) == 2 && dsm::quad_strip_waves(5, true) == 3 &&
+              dsm::quad_strip_waves(8, true) == 3 && dsm::quad_strip_waves(15, true) == 3 &&
+              dsm::quad_strip_waves(16, true) == 4 && dsm::quad_strip_waves(4, false) == 4 &&
+              dsm::quad_strip_waves(9, false) == 3,
+          "waves of a strip in a four-strip work-group");
 }
 
 // The 64-ary search of a sparse launch, lane by lane, against a linear scan:
@@ -1453,6 +1479,7 @@ int main(int argc, char** argv) {
     check_init_and_chunks();
     check_facts();
     check_chunk_search();
+    check_round_end_waves();
     check_init_rejections();
     check_init_static();
     check_blocked_addressing(DSM_REPLICAS_BLOCKED);

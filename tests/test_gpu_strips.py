@@ -63,6 +63,10 @@ def padding(ar, flat):
     (SPARSE_130, 2, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_FLIP, 1, False),
     (SPARSE_64, 6, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_ZERO, 0, False),
     (SPARSE_4100, 2, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 2, True),
+    (DENSE, 4, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_ZERO, 1, True),
+    (DENSE, 5, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_FLIP, 0, True),
+    (DENSE, 15, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_FLIP, 2, True),
+    (DENSE, 9, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 0, True),
     (DENSE, 17, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0, True),
     (DENSE, 33, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 1, True),
     (DENSE, 64, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_ZERO, 2, True),
