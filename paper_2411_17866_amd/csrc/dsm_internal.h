@@ -50,6 +50,19 @@ constexpr int even_waves(int n, int most) {
 constexpr int quad_strip_waves(int n, bool adamw) {
     return even_waves(n, adamw && n < kMaxRoundEndWaves ? 3 : 4);
 }
+// Waves of the round end that takes one strip in a work-group.  SGD: 16; AdamW:
+// 8 (16 workers of 30M parameters: AdamW 65.3% (contiguous) and 72.6%
+// (state-blocked) of 8 TB/s with 16 waves, 68.0% and 75.4% with 8; SGD 73.9% and
+// 83.8% with 16, 70.0% and 78.9% with 8).  Where a second turn would leave three
+// quarters of them or more idle, even turns: deterministic, 25M elements of all
+// workers, contiguous, SGD with 17 workers 69.2 us with 16 waves, 62.7 us with 9;
+// with 20 workers 64.1 and 61.2 us; AdamW with 9 workers 104 us with 8 waves, 100
+// us with 5.  Beyond, all waves: SGD with 24 workers 59.0 us with 16, 59.6 us
+// with 12 (state-blocked 55.8 and 58.6 us).
+constexpr int strip_waves(int n, bool adamw) {
+    const int most = adamw ? kMaxRoundEndWaves / 2 : kMaxRoundEndWaves;
+    return n <= most + most / 4 ? even_waves(n, most) : most;
+}
 // Arena alignment of every tensor, in elements (256 bytes).
 constexpr int64_t kTensorAlign = 64;
 constexpr int kMaxWorkers = 64;

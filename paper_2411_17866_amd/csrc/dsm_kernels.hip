@@ -1034,14 +1034,8 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
                                    hipStream_t st) {
     constexpr int strips = PIECE ? kQuadWaves : 1;
     const dim3 grid = PIECE ? quad_grid(n_chunks, a.rl) : strip_grid(n_chunks, a.rl);
-    // AdamW's waves take longer and less evenly than SGD's, and a barrier over
-    // 16 of them waits longer than two shares per wave of 8 do: n = 16, 30M
-    // parameters, AdamW 65.3% (contiguous) and 72.6% (state-blocked) of 8 TB/s
-    // with 16 waves, 68.0% and 75.4% with 8; SGD 73.9% and 83.8%, 70.0% and
-    // 78.9%.
-    constexpr int max_waves = BASE == kBaseSgd ? kMaxRoundEndWaves : kMaxRoundEndWaves / 2;
-    int workers = PIECE ? quad_strip_waves(a.gs.n, BASE == kBaseAdamW)
-                        : (a.gs.n < max_waves ? a.gs.n : max_waves);
+    constexpr bool adamw = BASE == kBaseAdamW;
+    int workers = PIECE ? quad_strip_waves(a.gs.n, adamw) : strip_waves(a.gs.n, adamw);
     // A grid dimension holds fewer than 2^32 threads.
     while (static_cast<int64_t>(grid.x) * workers * strips * kWave >= (int64_t(1) << 32))
         workers /= 2;

@@ -700,6 +700,17 @@ void check_round_end_waves() {
                 CHECK(dsm::quad_strip_waves(n, adamw) * dsm::kQuadWaves <= dsm::kMaxRoundEndWaves,
                       "%d workers: a work-group holds 16 waves", n);
     }
+    for (int n = 1; n <= 64; ++n)
+        for (bool adamw : {false, true}) {
+            const int most = adamw ? 8 : 16, waves = dsm::strip_waves(n, adamw);
+            CHECK(waves <= most && waves <= n && (n + waves - 1) / waves == (n + most - 1) / most,
+                  "%d workers on %d waves", n, waves);
+        }
+    CHECK(dsm::strip_waves(9, true) == 5 && dsm::strip_waves(10, true) == 5 &&
+              dsm::strip_waves(11, true) == 8 && dsm::strip_waves(17, false) == 9 &&
+              dsm::strip_waves(20, false) == 10 && dsm::strip_waves(21, false) == 16 &&
+              dsm::strip_waves(64, false) == 16,
+          "waves of a strip in a work-group of its own");
     CHECK(dsm::quad_strip_waves(4, true) == 2 && dsm::quad_strip_waves(5, true) == 3 &&
               dsm::quad_strip_waves(8, true) == 3 && dsm::quad_strip_waves(15, true) == 3 &&
               dsm::quad_strip_waves(16, true) == 4 && dsm::quad_strip_waves(4, false) == 4 &&

@@ -69,6 +69,8 @@ def padding(ar, flat):
     (DENSE, 9, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 0, True),
     (DENSE, 17, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0, True),
     (DENSE, 33, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 1, True),
+    (DENSE, 9, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 1, True),
+    (DENSE, 20, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_DET, 2, True),
     (DENSE, 64, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_ZERO, 2, True),
     (DENSE, 7, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 2, False),
 ])
