@@ -1005,18 +1005,28 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
 
 // Work-groups of the round end per CU, by waves per work-group.  Many waves
 // of a group wait for its last, so more waves are resident than in a local
-// step, and fewer groups the larger they are (swept 2 to 24 at GPT-2 small to
-// xl; deterministic, one worker 77.4% with 10-12, 72% with 8, 74% with 14).  The
-// randomized one has one more, or two with one worker.  From eight waves a group on,
-// the 32 waves that a CU holds are the limit: four groups of eight, two of sixteen.
-constexpr int round_end_groups(int waves, bool randomized) {
+// step, and fewer groups the larger they are.  AdamW: swept 2 to 24 at GPT-2
+// small to xl; deterministic, one worker 77.4% with 10-12, 72% with 8, 74% with
+// 14; the randomized one has one more, or two with one worker.  SGD loads fewer
+// streams a wave and has little arithmetic: swept 4 to 32 at 8M to 400M elements
+// of all workers, deterministic, both from x and from replicas; 25M, contiguous,
+// from x, with AdamW's counts and with its own: one worker 125 and 117 us, two 92
+// and 84 us, three 86 and 74 us, four 76 and 67 us, five 76 and 67 us.  From
+// eight waves a group on, the 32 waves that a CU holds are the limit, but not the
+// LDS: waves that are done make room for the next group's while the first of
+// theirs takes the global step.
+constexpr int round_end_groups(int waves, bool randomized, bool adamw) {
+    if (!adamw) {
+        constexpr int sgd[] = {16, 12, 10, 8, 6};
+        return waves <= 5 ? sgd[waves - 1] : 5;
+    }
     const int groups = waves == 1 ? 12 : waves == 2 ? 8 : waves == 3 ? 6 : waves == 4 ? 5 : 4;
     return groups + (randomized ? (waves == 1 ? 2 : 1) : 0);
 }
 constexpr bool round_end_groups_attainable() {
     for (int waves = 1; waves <= kMaxRoundEndWaves; ++waves)
-        if (!attainable(round_end_groups(waves, false)) || !attainable(round_end_groups(waves, true)))
-            return false;
+        for (int which = 0; which < 4; ++which)
+            if (!attainable(round_end_groups(waves, which & 1, which & 2))) return false;
     return true;
 }
 static_assert(round_end_groups_attainable(), "work-groups of the round end");
@@ -1041,7 +1051,7 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
         workers /= 2;
     const int groups = PIECE ? kAllWaves
                              : waves_for(n_chunks, a.rl, 4 * a.gs.n + 2,
-                                         round_end_groups(workers, KIND == 2));
+                                         round_end_groups(workers, KIND == 2, adamw));
     const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
     const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
     const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
