@@ -1049,9 +1049,14 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
     // A grid dimension holds fewer than 2^32 threads.
     while (static_cast<int64_t>(grid.x) * workers * strips * kWave >= (int64_t(1) << 32))
         workers /= 2;
-    const int groups = PIECE ? kAllWaves
-                             : waves_for(n_chunks, a.rl, 4 * a.gs.n + 2,
-                                         round_end_groups(workers, KIND == 2, adamw));
+    // Four strips of one worker are as many waves as four work-groups of one, and
+    // held to 16 (AdamW) or 20 (SGD): 25M elements, state-blocked, randomized
+    // round end from x with its second pass 207 and 180 us with all waves, 200
+    // and 175 us; from replicas at 100M, contiguous, 867 and 723 us, 830 and 691
+    // us.  With more workers the barriers hold them back enough.
+    const int groups = waves_for(
+        n_chunks, a.rl, 4 * a.gs.n + 2,
+        !PIECE ? round_end_groups(workers, KIND == 2, adamw) : a.gs.n > 1 ? kAllWaves : adamw ? 4 : 5);
     const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
     const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
     const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
