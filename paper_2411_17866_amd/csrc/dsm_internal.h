@@ -84,11 +84,14 @@ struct RepLayout {
     int64_t block_stride;
     int64_t copy_stride;
     int32_t shift;
-    // Of the problem, not of the buffer: 0, or where most strip groups of its
-    // chunks hold no elements (many tensors far shorter than a chunk), the number
-    // of those that do; its launches then go over these only.
-    uint32_t sparse_groups;
-    int64_t groups() const { return sparse_groups; }
+    // Of the problem, not of the buffer, set by problem_facts().  groups: 0, or
+    // where most strip groups of its chunks hold no elements (many tensors far
+    // shorter than a chunk), the number of those that do; its launches then go
+    // over these only.  cached: its arenas are small enough to stay in the
+    // caches between calls.
+    uint32_t facts;
+    int64_t groups() const { return facts & 0x7fffffffu; }
+    bool cached() const { return facts >> 31 != 0; }
 };
 // Sparse from half the groups empty on.  A wave of a sparse launch searches for
 // its chunk, ~1 us; the waves it saves cost their dispatch (125 tensors of 64K
@@ -97,6 +100,15 @@ struct RepLayout {
 // elements: 81 us, 86 us before).
 constexpr bool sparse_chunks(int64_t groups, int64_t n_chunks) {
     return 2 * groups <= n_chunks * (kStrips / kGroupStrips);
+}
+// Three eighths of the 256 MB last-level cache: problems of 106 MB taking turns
+// already lose 2% to plain accesses.
+constexpr int64_t kCachedBytes = int64_t(96) << 20;
+// RepLayout::facts of a problem with `groups` strip groups that hold elements,
+// n_chunks chunks and `bytes` of arenas.
+constexpr uint32_t problem_facts(int64_t groups, int64_t n_chunks, int64_t bytes) {
+    return (sparse_chunks(groups, n_chunks) ? static_cast<uint32_t>(groups) : 0u) |
+           (bytes <= kCachedBytes ? 0x80000000u : 0u);
 }
 // n contiguous copies of d_pad elements.
 inline RepLayout contiguous_copies(int64_t d_pad) { return RepLayout{0, d_pad, 62, 0}; }

@@ -3,8 +3,8 @@
 //
 // Every kernel streams fp32 arenas: a wave takes one strip (64 lanes x one
 // float4 = 256 elements, 1 KiB per stream) of one chunk of one tensor, with
-// 128-bit loads and stores (nontemporal, but for a model x that all workers
-// read in turn), consecutive lanes on consecutive 16-byte groups, and every
+// 128-bit loads and stores, nontemporal where nothing reads the line again soon
+// (Policy, below), consecutive lanes on consecutive 16-byte groups, and every
 // element is read and written once per pass.
 // Nothing here is a dense contraction, so there is no MFMA; the bound is HBM
 // bandwidth, and what is left to gain is how close the mix of read and write
@@ -28,26 +28,32 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-// Nontemporal at every size, also where a problem fits the 256 MB last-level
-// cache: plain accesses displace what the program's other kernels keep there,
-// and wait for its stores to be written back.  Fused rounds of H = 4, plain
-// against nontemporal: alone, 25-41 us against 23-44 us at 2M elements of all
-// workers, within 4% on average at 0.25M to 1M and at 3M to 5M; with a 256 MB
-// read before each of the four calls, which then finds its buffer gone, 340-367
-// us against 248-266 us for the reads and the round at 2M; with a 256 MB fill
-// before each call 193-225 us against 183-207 us at 3M.
-__device__ __forceinline__ f4 ntload(const f4* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void ntstore(f4 v, f4* p) { __builtin_nontemporal_store(v, p); }
+// Cache policy of a launch's streams.
+// kStream: nontemporal loads and stores, for arenas that have left every cache
+// before they are read again.
+// kShared: the same, but for a local step's starting point, which in the
+// interleaved order the n workers read one soon after the other: a plain load
+// leaves it in the caches for the others, and x comes from HBM once.
+// kCached: plain loads and stores, for problems whose arenas are still in the
+// 256 MB last-level cache at the next call (RepLayout::cached()): rounds of 1.1M
+// elements, n = 2, 27.8 us against 36.6 us with nontemporal ones; 8 x 128K,
+// n = 4 (75 MB), 74.4 us against 84.0 us; but 161 MB 167.9 against 165.2 us and
+// 510 MB 344 against 317 us.
+enum Policy { kStream, kShared, kCached };
 
-// The load of a local step's starting point.  SHARED: in the interleaved order
-// the n workers read it one soon after the other; a plain load leaves it in the
-// caches for the others, and x comes from HBM once.
-template <bool SHARED>
-__device__ __forceinline__ f4 load_start(const f4* p) {
-    if constexpr (SHARED)
+template <int POLICY>
+__device__ __forceinline__ f4 load(const f4* p) {
+    if constexpr (POLICY == kCached)
         return *p;
     else
-        return ntload(p);
+        return __builtin_nontemporal_load(p);
+}
+template <int POLICY>
+__device__ __forceinline__ void store(f4 v, f4* p) {
+    if constexpr (POLICY == kCached)
+        *p = v;
+    else
+        __builtin_nontemporal_store(v, p);
 }
 
 // Stores the first k (1..3) lanes of v: the ragged end of a tensor.
@@ -59,9 +65,10 @@ __device__ __forceinline__ void store_head(f4 v, float* p, int k) {
 
 // Stores v at p: the whole group when its four lanes are inside the chunk
 // (valid >= 4), else only the valid lanes.
+template <int POLICY>
 __device__ __forceinline__ void store_vec(f4 v, f4* p, int valid) {
     if (valid >= 4)
-        ntstore(v, p);
+        store<POLICY>(v, p);
     else
         store_head(v, reinterpret_cast<float*>(p), valid);
 }
@@ -216,26 +223,27 @@ __device__ __forceinline__ void adamw4(f4& x, f4 g, f4& m, f4& v, float lam, con
 // moments sit at rep_index(ml.g / ml.s1 / ml.s2, w, e) of their buffers.  The two may be the
 // same memory, so neither pointer is __restrict__; each lane loads every
 // stream of its group before it stores.
-template <bool SHARED>
+template <int POLICY>
 __global__ __launch_bounds__(kBlockThreads) void k_local_adamw(
     const Chunk* __restrict__ chunks, Rows rows, float* x_rep, RepLayout rl, const float* x_src,
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1,
     float* __restrict__ s2, StateLayout ml, int worker0, int n_workers, AdamScalars sc) {
     int64_t w;
-    const Strip st = local_strip<SHARED>(chunks, rows, worker0, n_workers, w);
+    const Strip st = local_strip<POLICY == kShared>(chunks, rows, worker0, n_workers, w);
     const int q = lane_id();
     if (q >= st.nq) return;
     f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
     f4* mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, st.e0)) + q;
     f4* vp = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, w, st.e0)) + q;
-    f4 x = load_start<SHARED>(reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
-    const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
-    f4 m = ntload(mp), v = ntload(vp);
+    f4 x = load<POLICY == kShared ? kCached : POLICY>(
+        reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
+    const f4 g = load<POLICY>(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
+    f4 m = load<POLICY>(mp), v = load<POLICY>(vp);
     adamw4(x, g, m, v, st.c.decay ? sc.wd : 0.0f, sc);
     const int valid = st.valid0 - 4 * q;
-    store_vec(x, xp, valid);
-    store_vec(m, mp, valid);
-    store_vec(v, vp, valid);
+    store_vec<POLICY>(x, xp, valid);
+    store_vec<POLICY>(m, mp, valid);
+    store_vec<POLICY>(v, vp, valid);
 }
 
 // ---------------------------------------------------------------- SGD + momentum
@@ -248,24 +256,25 @@ __device__ __forceinline__ void sgdm4(f4& x, f4 g, f4& m, const SgdScalars& s) {
     x = x - st;
 }
 
-template <bool SHARED>
+template <int POLICY>
 __global__ __launch_bounds__(kBlockThreads) void k_local_sgdm(
     const Chunk* __restrict__ chunks, Rows rows, float* x_rep, RepLayout rl, const float* x_src,
     RepLayout sl, const float* __restrict__ g_rep, float* __restrict__ s1, StateLayout ml,
     int worker0, int n_workers, SgdScalars sc) {
     int64_t w;
-    const Strip st = local_strip<SHARED>(chunks, rows, worker0, n_workers, w);
+    const Strip st = local_strip<POLICY == kShared>(chunks, rows, worker0, n_workers, w);
     const int q = lane_id();
     if (q >= st.nq) return;
     f4* xp = reinterpret_cast<f4*>(x_rep + rep_index(rl, w, st.e0)) + q;
     f4* mp = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, w, st.e0)) + q;
-    f4 x = load_start<SHARED>(reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
-    const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
-    f4 m = ntload(mp);
+    f4 x = load<POLICY == kShared ? kCached : POLICY>(
+        reinterpret_cast<const f4*>(x_src + rep_index(sl, w, st.e0)) + q);
+    const f4 g = load<POLICY>(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, w, st.e0)) + q);
+    f4 m = load<POLICY>(mp);
     sgdm4(x, g, m, sc);
     const int valid = st.valid0 - 4 * q;
-    store_vec(x, xp, valid);
-    store_vec(m, mp, valid);
+    store_vec<POLICY>(x, xp, valid);
+    store_vec<POLICY>(m, mp, valid);
 }
 
 // ---------------------------------------------------------------- global step
@@ -281,7 +290,7 @@ __device__ __forceinline__ float sign_of(float u) {
 // multiplication by 1/n), every replica's load in flight together; N == 0:
 // runtime count, kReplicaBatch loads in flight at a time.
 constexpr int kReplicaBatch = 4;
-template <int N>
+template <int N, int POLICY>
 __device__ __forceinline__ f4 worker_mean_diff(f4 xv, const float* __restrict__ x_rep,
                                                const RepLayout& rl, int64_t e0, int q,
                                                const GlobalScalars& s) {
@@ -289,7 +298,7 @@ __device__ __forceinline__ f4 worker_mean_diff(f4 xv, const float* __restrict__ 
         f4 r[N];
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            r[i] = ntload(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i, e0)) + q);
+            r[i] = load<POLICY>(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i, e0)) + q);
         f4 acc = xv - r[0];
 #pragma unroll
         for (int i = 1; i < N; ++i) acc = acc + (xv - r[i]);
@@ -301,8 +310,7 @@ __device__ __forceinline__ f4 worker_mean_diff(f4 xv, const float* __restrict__ 
 #pragma unroll
             for (int k = 0; k < kReplicaBatch; ++k)
                 if (i0 + k < s.n)
-                    r[k] =
-                        ntload(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i0 + k, e0)) + q);
+                    r[k] = load<POLICY>(reinterpret_cast<const f4*>(x_rep + rep_index(rl, i0 + k, e0)) + q);
 #pragma unroll
             for (int k = 0; k < kReplicaBatch; ++k)
                 if (i0 + k < s.n) {
@@ -366,7 +374,7 @@ __device__ __forceinline__ f4 global_adamw4(f4 x, f4 delta, f4& m, f4& v, float 
     return x - st;
 }
 
-template <int N, int RULE, bool BCAST>
+template <int N, int RULE, bool BCAST, int POLICY>
 __global__ __launch_bounds__(kBlockThreads) void k_global_det(
     const Chunk* __restrict__ chunks, Rows rows, float* __restrict__ x, float* __restrict__ m,
     float* __restrict__ v, float* __restrict__ x_rep, RepLayout rl, GlobalScalars sc) {
@@ -379,10 +387,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_det(
     f4* __restrict__ vp = reinterpret_cast<f4*>(v + st.e0) + q;
     const float lam = st.c.decay ? sc.lam : 0.0f;
     const int valid = st.valid0 - 4 * q;
-    const f4 xv = ntload(xp);
-    f4 mv = ntload(mp), vv;
-    if (RULE == kRuleGlobalAdamW) vv = ntload(vp);
-    const f4 delta = worker_mean_diff<N>(xv, x_rep, rl, st.e0, q, sc);
+    const f4 xv = load<POLICY>(xp);
+    f4 mv = load<POLICY>(mp), vv;
+    if (RULE == kRuleGlobalAdamW) vv = load<POLICY>(vp);
+    const f4 delta = worker_mean_diff<N, POLICY>(xv, x_rep, rl, st.e0, q, sc);
     f4 xn;
     if constexpr (RULE == kRuleSignMomentum) {
         const f4 u = momentum4(mv, delta, sc);
@@ -401,13 +409,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_det(
         xn = model4(xv, u, lam, sc);
     } else {
         xn = global_adamw4(xv, delta, mv, vv, lam, sc);
-        store_vec(vv, vp, valid);
+        store_vec<POLICY>(vv, vp, valid);
     }
-    store_vec(xn, xp, valid);
-    store_vec(mv, mp, valid);
+    store_vec<POLICY>(xn, xp, valid);
+    store_vec<POLICY>(mv, mp, valid);
     if (BCAST) {
         for (int i = 0; i < n; ++i)
-            store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
+            store_vec<POLICY>(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
     }
 }
 
@@ -451,7 +459,7 @@ __device__ __forceinline__ uint32_t abs_max(f4 u, int valid) {
 // two levels with plain loads and stores and no atomics.  Level one: each
 // work-group (a quad) stores its largest |u| in its own word.  Level two is
 // k_bound_reduce.
-template <int N>
+template <int N, int POLICY>
 __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
     const Chunk* __restrict__ chunks, Rows rows, const float* __restrict__ x,
     float* __restrict__ m, const float* __restrict__ x_rep, RepLayout rl,
@@ -462,13 +470,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass1(
     uint32_t maxbits = 0;
     if (q < st.nq) {
         f4* __restrict__ mp = reinterpret_cast<f4*>(m + st.e0) + q;
-        const f4 xv = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
-        f4 mv = ntload(mp);
-        const f4 delta = worker_mean_diff<N>(xv, x_rep, rl, st.e0, q, sc);
+        const f4 xv = load<POLICY>(reinterpret_cast<const f4*>(x + st.e0) + q);
+        f4 mv = load<POLICY>(mp);
+        const f4 delta = worker_mean_diff<N, POLICY>(xv, x_rep, rl, st.e0, q, sc);
         const int valid = st.valid0 - 4 * q;  // lanes inside the tensor
         const f4 u = momentum4(mv, delta, sc);
-        store_vec(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
-        store_vec(mv, mp, valid);
+        store_vec<POLICY>(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
+        store_vec<POLICY>(mv, mp, valid);
         maxbits = abs_max(u, valid);
     }
     maxbits = block_max<kBlockThreads>(maxbits, lds);
@@ -544,7 +552,7 @@ __device__ __forceinline__ float rand_sign(float u, uint32_t w, double B) {
 //
 // FOLD: level two of the bound as well.  Each wave takes the maximum of its
 // tensor's words itself, and the wave of the tensor's first strip stores it.
-template <int MODE, bool BCAST, bool FOLD>
+template <int MODE, bool BCAST, int POLICY, bool FOLD>
 __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
     const Chunk* __restrict__ chunks, Rows rows, float* __restrict__ x, float* __restrict__ x_rep,
     RepLayout rl, const float* __restrict__ u_in, BoundWords bw, GlobalScalars sc) {
@@ -555,8 +563,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
     f4* __restrict__ xp = reinterpret_cast<f4*>(x + st.e0) + q;
     f4 xv, u;
     if (on) {
-        xv = ntload(xp);
-        u = ntload(reinterpret_cast<const f4*>(u_in + st.e0) + q);
+        xv = load<POLICY>(xp);
+        u = load<POLICY>(reinterpret_cast<const f4*>(u_in + st.e0) + q);
     }
     uint32_t bbits;
     if constexpr (FOLD) {
@@ -578,10 +586,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_global_rand_pass2(
     if (!bound_finite) S = f4{undefined, undefined, undefined, undefined};
     const f4 xn = model4(xv, S, lam, sc);
     const int valid = st.valid0 - 4 * q;
-    store_vec(xn, xp, valid);
+    store_vec<POLICY>(xn, xp, valid);
     if (BCAST) {
         for (int i = 0; i < sc.n; ++i)
-            store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
+            store_vec<POLICY>(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
     }
 }
 
@@ -605,7 +613,7 @@ constexpr int kBaseSgd = 1;
 // step.  PIECE false: a work-group takes one strip (KIND 2: and raises its
 // bound word by an atomic max).  PIECE true (KIND 2): it takes the four strips
 // of a bound word side by side and stores the word.
-template <int BASE, int KIND, bool PIECE>
+template <int BASE, int KIND, bool PIECE, int POLICY>
 __global__ __launch_bounds__(kMaxRoundEndWaves * kWave) void k_round_end(
     const Chunk* __restrict__ chunks, Rows rows, float* x, float* __restrict__ m, float* x_rep,
     RepLayout rl, const float* x_src, RepLayout sl, const float* __restrict__ g_rep,
@@ -628,24 +636,24 @@ __global__ __launch_bounds__(kMaxRoundEndWaves * kWave) void k_round_end(
     f4* __restrict__ mp = reinterpret_cast<f4*>(m + st.e0) + q;
     f4 xv, mv;
     if (w0 == 0 && on) {
-        xv = ntload(xp);
-        mv = ntload(mp);
+        xv = load<POLICY>(xp);
+        mv = load<POLICY>(mp);
     }
     const float lam_local = st.c.decay ? as.wd : 0.0f;
     for (int i = w0; i < gs.n && on; i += workers) {
         f4* __restrict__ s1p = reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, st.e0)) + q;
-        f4 xi = ntload(reinterpret_cast<const f4*>(x_src + rep_index(sl, i, st.e0)) + q);
-        const f4 g = ntload(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, st.e0)) + q);
-        f4 mi = ntload(s1p);
+        f4 xi = load<POLICY>(reinterpret_cast<const f4*>(x_src + rep_index(sl, i, st.e0)) + q);
+        const f4 g = load<POLICY>(reinterpret_cast<const f4*>(g_rep + rep_index(ml.g, i, st.e0)) + q);
+        f4 mi = load<POLICY>(s1p);
         if (BASE == kBaseAdamW) {
             f4* __restrict__ s2p = reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, st.e0)) + q;
-            f4 vi = ntload(s2p);
+            f4 vi = load<POLICY>(s2p);
             adamw4(xi, g, mi, vi, lam_local, as);
-            store_vec(vi, s2p, valid);
+            store_vec<POLICY>(vi, s2p, valid);
         } else {
             sgdm4(xi, g, mi, ss);
         }
-        store_vec(mi, s1p, valid);
+        store_vec<POLICY>(mi, s1p, valid);
         ends[i * kWave] = xi;
     }
     __syncthreads();
@@ -654,16 +662,16 @@ __global__ __launch_bounds__(kMaxRoundEndWaves * kWave) void k_round_end(
         for (int i = 1; i < gs.n; ++i) acc = acc + (xv - ends[i * kWave]);
         const f4 delta = gs.n_pow2 ? acc * gs.inv_n : acc / gs.n_f;
         const f4 u = momentum4(mv, delta, gs);
-        store_vec(mv, mp, valid);
+        store_vec<POLICY>(mv, mp, valid);
         if (KIND == 2) {
-            store_vec(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
+            store_vec<POLICY>(u, reinterpret_cast<f4*>(u_out + st.e0) + q, valid);
             maxbits = max(maxbits, abs_max(u, valid));
         } else {
             const f4 xn = model4(xv, sign4(u), st.c.decay ? gs.lam : 0.0f, gs);
-            store_vec(xn, xp, valid);
+            store_vec<POLICY>(xn, xp, valid);
             if (KIND == 1) {
                 for (int i = 0; i < gs.n; ++i)
-                    store_vec(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q,
+                    store_vec<POLICY>(xn, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q,
                               valid);
             }
         }
@@ -697,16 +705,17 @@ __global__ __launch_bounds__(kBlockThreads) void k_clear_words(uint4* __restrict
 // ---------------------------------------------------------------- sync / init
 
 // Synchronisation step: x_rep[i] <- x for every replica.
+template <int POLICY>
 __global__ __launch_bounds__(kBlockThreads) void k_broadcast(
     const Chunk* __restrict__ chunks, Rows rows, const float* __restrict__ x, float* __restrict__ x_rep,
     RepLayout rl, int n) {
     const Strip st = strip_of(chunks, rows);
     const int q = lane_id();
     if (q >= st.nq) return;
-    const f4 v = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
+    const f4 v = load<POLICY>(reinterpret_cast<const f4*>(x + st.e0) + q);
     const int valid = st.valid0 - 4 * q;
     for (int i = 0; i < n; ++i)
-        store_vec(v, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
+        store_vec<POLICY>(v, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
 }
 
 // Algorithm 1 initialisation: m = 0, replicas = x, base state = 0.
@@ -718,15 +727,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_init(
     const int q = lane_id();
     if (q >= st.nq) return;
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    const f4 xv = ntload(reinterpret_cast<const f4*>(x + st.e0) + q);
+    const f4 xv = load<kStream>(reinterpret_cast<const f4*>(x + st.e0) + q);
     const int valid = st.valid0 - 4 * q;
-    store_vec(zero, reinterpret_cast<f4*>(m + st.e0) + q, valid);
-    if (v != nullptr) store_vec(zero, reinterpret_cast<f4*>(v + st.e0) + q, valid);
+    store_vec<kStream>(zero, reinterpret_cast<f4*>(m + st.e0) + q, valid);
+    if (v != nullptr) store_vec<kStream>(zero, reinterpret_cast<f4*>(v + st.e0) + q, valid);
     for (int i = 0; i < n; ++i) {
-        store_vec(xv, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
-        store_vec(zero, reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, st.e0)) + q, valid);
+        store_vec<kStream>(xv, reinterpret_cast<f4*>(x_rep + rep_index(rl, i, st.e0)) + q, valid);
+        store_vec<kStream>(zero, reinterpret_cast<f4*>(s1 + rep_index(ml.s1, i, st.e0)) + q, valid);
         if (s2 != nullptr)
-            store_vec(zero, reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, st.e0)) + q, valid);
+            store_vec<kStream>(zero, reinterpret_cast<f4*>(s2 + rep_index(ml.s2, i, st.e0)) + q, valid);
     }
 }
 
@@ -768,7 +777,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_read(const float* __re
     const f4* __restrict__ p = reinterpret_cast<const f4*>(buf) + static_cast<int64_t>(wi) * kPieceVec;
     uint32_t acc = 0;
     for (int q = threadIdx.x; q < kPieceVec; q += kBlockThreads) {
-        const f4 v = ntload(p + q);
+        const f4 v = load<kStream>(p + q);
         acc ^= __float_as_uint(v.x) ^ __float_as_uint(v.y) ^ __float_as_uint(v.z) ^
                __float_as_uint(v.w);
     }
@@ -788,7 +797,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_stream_write(float* __restric
     f4* __restrict__ p = reinterpret_cast<f4*>(buf) + static_cast<int64_t>(wi) * kPieceVec;
     const float value = __uint_as_float(pattern);
     const f4 v = {value, value, value, value};
-    for (int q = threadIdx.x; q < kPieceVec; q += kBlockThreads) ntstore(v, p + q);
+    for (int q = threadIdx.x; q < kPieceVec; q += kBlockThreads) store<kStream>(v, p + q);
 }
 
 // Launch shape.  All kernels are bound by HBM, and what decides how much of
@@ -951,8 +960,9 @@ hipError_t launch_local_adamw(const Chunk* chunks, int64_t n_chunks, float* x_re
                               const AdamScalars& sc, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    launch_local(k_local_adamw<false>, chunks, n_chunks, rl, map, 4, kAdamWWaves, n_workers, st,
-                 x_rep, rl, x_src, sl, g_rep, s1, s2, ml, worker0, n_workers, sc);
+    launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kStream>, chunks, n_chunks, rl,
+                 map, 4, kAdamWWaves, n_workers, st, x_rep, rl, x_src, sl, g_rep, s1, s2, ml,
+                 worker0, n_workers, sc);
     return hipGetLastError();
 }
 
@@ -962,8 +972,9 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
                              int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n_workers, map);
-    launch_local(k_local_sgdm<false>, chunks, n_chunks, rl, map, 3, kSgdWaves, n_workers, st,
-                 x_rep, rl, x_src, sl, g_rep, s1, ml, worker0, n_workers, sc);
+    launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kStream>, chunks, n_chunks, rl,
+                 map, 3, kSgdWaves, n_workers, st, x_rep, rl, x_src, sl, g_rep, s1, ml, worker0,
+                 n_workers, sc);
     return hipGetLastError();
 }
 
@@ -982,11 +993,13 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
     if (n_chunks == 0) return hipSuccess;
     map = local_map(n_chunks, n, map);
     if (adamw)
-        launch_local(k_local_adamw<true>, chunks, n_chunks, rl, map, 4, kAdamWSharedWaves, n, st,
-                     x_rep, rl, x, single_copy(), g_rep, s1, s2, ml, 0, n, as);
+        launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kShared>, chunks, n_chunks,
+                     rl, map, 4, kAdamWSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1,
+                     s2, ml, 0, n, as);
     else
-        launch_local(k_local_sgdm<true>, chunks, n_chunks, rl, map, 3, kSgdSharedWaves, n, st,
-                     x_rep, rl, x, single_copy(), g_rep, s1, ml, 0, n, ss);
+        launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kShared>, chunks, n_chunks,
+                     rl, map, 3, kSgdSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1, ml,
+                     0, n, ss);
     return hipGetLastError();
 }
 
@@ -1046,8 +1059,9 @@ static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const 
         !PIECE ? round_end_groups(workers, KIND == 2, adamw) : a.gs.n > 1 ? kAllWaves : adamw ? 4 : 5);
     const unsigned ends = static_cast<unsigned>(strips * a.gs.n * kWave * sizeof(f4));
     const unsigned lds = ends > lds_for(groups) ? ends : lds_for(groups);
-    hipLaunchKernelGGL((k_round_end<BASE, KIND, PIECE>), grid, dim3(workers * strips * kWave), lds,
-                       st, chunks,
+    const auto kernel = a.rl.cached() ? k_round_end<BASE, KIND, PIECE, kCached>
+                                    : k_round_end<BASE, KIND, PIECE, kStream>;
+    hipLaunchKernelGGL(kernel, grid, dim3(workers * strips * kWave), lds, st, chunks,
                        rows_of(n_chunks, a.rl, 0), a.x, a.m, a.x_rep, a.rl, a.x_src, a.sl,
                        a.g_rep, a.s1, a.s2, a.u, a.bound.piece_max, a.ml, workers, a.as, a.ss,
                        a.gs);
@@ -1107,20 +1121,22 @@ static void launch_rand_rest(const Chunk* chunks, int64_t n_chunks, int n_tensor
                            rl.groups() > 0);
     if (n_chunks == 0) return;
     const int stores = broadcast ? sc.n + 1 : 1;
-#define DSM_PASS2(MODE, B)                                                                       \
-    do {                                                                                         \
-        if (fold)                                                                                \
-            launch_strips(k_global_rand_pass2<MODE, B, true>, chunks, n_chunks, rl, map,         \
-                          stores + 1, pass2_waves(stores), st, x, x_rep, rl, u, bw, sc);         \
-        else                                                                                     \
-            launch_strips(k_global_rand_pass2<MODE, B, false>, chunks, n_chunks, rl, map,        \
-                          stores + 1, pass2_waves(stores), st, x, x_rep, rl, u, bw, sc);         \
+#define DSM_PASS2(MODE, B, POLICY, FOLD)                                                        \
+    launch_strips(k_global_rand_pass2<MODE, B, POLICY, FOLD>, chunks, n_chunks, rl, map,        \
+                  stores + 1, pass2_waves(stores), st, x, x_rep, rl, u, bw, sc)
+#define DSM_PASS2_POLICY(MODE, B)                                                               \
+    do {                                                                                        \
+        if (!fold && !rl.cached()) DSM_PASS2(MODE, B, kStream, false);                            \
+        else if (!fold) DSM_PASS2(MODE, B, kCached, false);                                     \
+        else if (!rl.cached()) DSM_PASS2(MODE, B, kStream, true);                                 \
+        else DSM_PASS2(MODE, B, kCached, true);                                                 \
     } while (0)
     if (sc.mode == 1) {
-        if (broadcast) DSM_PASS2(1, true); else DSM_PASS2(1, false);
+        if (broadcast) DSM_PASS2_POLICY(1, true); else DSM_PASS2_POLICY(1, false);
     } else {
-        if (broadcast) DSM_PASS2(2, true); else DSM_PASS2(2, false);
+        if (broadcast) DSM_PASS2_POLICY(2, true); else DSM_PASS2_POLICY(2, false);
     }
+#undef DSM_PASS2_POLICY
 #undef DSM_PASS2
 }
 
@@ -1144,8 +1160,13 @@ template <int RULE, bool BCAST>
 static void launch_global_det_n(const Chunk* chunks, int64_t n_chunks, float* x, float* m,
                                 float* v, float* x_rep, RepLayout rl, const GlobalScalars& sc,
                                 int map, hipStream_t st) {
+    if (rl.cached()) {
+        launch_strips(k_global_det<0, RULE, BCAST, kCached>, chunks, n_chunks, rl, map, sc.n + 2,
+                      global_waves(sc.n), st, x, m, v, x_rep, rl, sc);
+        return;
+    }
 #define DSM_GLOBAL_DET(NW)                                                                       \
-    launch_strips(k_global_det<NW, RULE, BCAST>, chunks, n_chunks, rl, map, sc.n + 2,            \
+    launch_strips(k_global_det<NW, RULE, BCAST, kStream>, chunks, n_chunks, rl, map, sc.n + 2,            \
                   global_waves(sc.n), st, x, m, v, x_rep, rl, sc)
     switch (sc.n) {
         case 1: DSM_GLOBAL_DET(1); break;
@@ -1197,15 +1218,17 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
                               const BoundWords& bw, const GlobalScalars& sc, bool broadcast,
                               int map, hipStream_t st) {
     if (n_chunks > 0) {
-#define DSM_PASS1(NW)                                                                            \
-    launch_strips(k_global_rand_pass1<NW>, chunks, n_chunks, rl, kQuads, sc.n + 3,               \
+#define DSM_PASS1(NW, POLICY)                                                                    \
+    launch_strips(k_global_rand_pass1<NW, POLICY>, chunks, n_chunks, rl, kQuads, sc.n + 3,       \
                   pass1_waves(sc.n), st, x, m, x_rep, rl, u, bw.piece_max, sc)
-        switch (sc.n) {
-            case 1: DSM_PASS1(1); break;
-            case 2: DSM_PASS1(2); break;
-            case 4: DSM_PASS1(4); break;
-            case 8: DSM_PASS1(8); break;
-            default: DSM_PASS1(0); break;
+        if (rl.cached())
+            DSM_PASS1(0, kCached);
+        else switch (sc.n) {
+            case 1: DSM_PASS1(1, kStream); break;
+            case 2: DSM_PASS1(2, kStream); break;
+            case 4: DSM_PASS1(4, kStream); break;
+            case 8: DSM_PASS1(8, kStream); break;
+            default: DSM_PASS1(0, kStream); break;
         }
 #undef DSM_PASS1
     }
@@ -1216,8 +1239,8 @@ hipError_t launch_global_rand(const Chunk* chunks, int64_t n_chunks, int n_tenso
 hipError_t launch_broadcast(const Chunk* chunks, int64_t n_chunks, const float* x, float* x_rep,
                             RepLayout rl, int n, int map, hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    launch_strips(k_broadcast, chunks, n_chunks, rl, map, n + 1, copy_waves(n), st, x, x_rep, rl,
-                  n);
+    launch_strips(rl.cached() ? k_broadcast<kCached> : k_broadcast<kStream>, chunks, n_chunks, rl,
+                  map, n + 1, copy_waves(n), st, x, x_rep, rl, n);
     return hipGetLastError();
 }
 

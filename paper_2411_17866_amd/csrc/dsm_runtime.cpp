@@ -426,8 +426,9 @@ dsm_status init_context(const dsm_problem* problem, const dsm_buffers* caller, d
                         adamw ? " and s2_rep" : "", static_cast<long long>(gap),
                         static_cast<long long>(2 * gap), adamw ? " and 3x that" : "", nb);
     }
-    if (dsm::sparse_chunks(L.groups, L.n_chunks))
-        rep.sparse_groups = static_cast<uint32_t>(L.groups);
+    // x, m and the workers' buffers (u and v, where used, are two more copies).
+    const int64_t copies = 2 + int64_t(problem->n_workers) * (adamw ? 4 : 3);
+    rep.facts = dsm::problem_facts(L.groups, L.n_chunks, 4 * copies * L.arena_elems);
     if (L.workspace_bytes > 0) {
         if (!b->workspace) return fail(nullptr, DSM_ERR_INVALID_ARG, "workspace is NULL");
         if (!aligned256(b->workspace))

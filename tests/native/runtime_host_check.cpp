@@ -13,8 +13,8 @@
 //     (the replica, or x after a global step without broadcast), with the
 //     replica addressing of both replica layouts;
 //   * the fp32 coefficients formed on the host, against long double;
-//   * the strip groups that a launch goes over, the chunk table's group index and
-//     the search over it, and the bound words as uploaded;
+//   * the facts a launch is dispatched by (strip groups, cached), the chunk table's
+//     group index and the search over it, and the bound words as uploaded;
 //   * how the round end's workers are shared over waves;
 //   * error paths: no device, failed launches, bad hyperparameters, NULLs;
 //   * contexts driven from several threads at once (also built with the
@@ -591,14 +591,14 @@ void check_init_and_chunks() {
     }
 }
 
-// Strip groups (2048 elements, 8 of a chunk's 16384) that hold elements, whether
-// a problem's launches go over these only, and the words of the randomized
-// sign's bound, written out from the sizes alone.
-struct Groups {
+// Strip groups (2048 elements, 8 of a chunk's 16384) that hold elements, the
+// facts that every launch of a problem is dispatched by, and the words of the
+// randomized sign's bound, written out from the sizes alone.
+struct Facts {
     std::vector<uint32_t> group0;  // of each chunk
     int64_t groups = 0, n_chunks = 0, max_words = 0;
-    bool sparse = false;
-    explicit Groups(const Problem& P) {
+    bool sparse = false, cached = false;
+    Facts(const Problem& P, int64_t arena) {
         for (int64_t ne : P.numel) {
             max_words = std::max<int64_t>(max_words, (ne + 16383) / 16384 * 16);
             for (int64_t left = ne; left > 0; left -= 16384, ++n_chunks) {
@@ -607,15 +607,17 @@ struct Groups {
             }
         }
         sparse = groups * 2 <= n_chunks * 8;
+        const int64_t per_worker = P.p.base == DSM_BASE_ADAMW ? 4 : 3;
+        cached = (2 + P.p.n_workers * per_worker) * arena * 4 <= 96 * 1024 * 1024;
     }
 };
 
-// Every launch of P is told of its strip groups, the uploaded table holds the
-// group index, and the upload zeroes the bounds.
-void check_groups_of(const Problem& P, bool want_sparse, const char* what) {
+// Every launch of P carries its facts, the uploaded table its group index, and
+// the upload zeroes the bounds.
+void check_facts_of(const Problem& P, bool want_sparse, bool want_cached, const char* what) {
     Buffers B(P, true, false);
-    const Groups f(P);
-    CHECK(f.sparse == want_sparse, "%s: the case is what it claims", what);
+    const Facts f(P, B.arena);
+    CHECK(f.sparse == want_sparse && f.cached == want_cached, "%s: the case is what it claims", what);
     const bool adamw = P.p.base == DSM_BASE_ADAMW;
     const dsm_local_hparams lh = adamw ? adam_hp() : sgd_hp();
     const dsm_global_hparams det = glob_hp(), rnd = glob_hp(DSM_SIGN_RAND_FLIP);
@@ -647,6 +649,7 @@ void check_groups_of(const Problem& P, bool want_sparse, const char* what) {
         CHECK(l.rl.groups() == (f.sparse ? f.groups : 0), "%s: %s over %lld strip groups, not %lld",
               what, l.kind.c_str(), static_cast<long long>(l.rl.groups()),
               static_cast<long long>(f.sparse ? f.groups : 0));
+        CHECK(l.rl.cached() == f.cached, "%s: %s cached %d", what, l.kind.c_str(), l.rl.cached());
         const bool bound = l.kind == "round_end" || l.kind == "global_rand";
         CHECK(l.max_words == (bound ? f.max_words : -1), "%s: %s with %lld words at most", what,
               l.kind.c_str(), static_cast<long long>(l.max_words));
@@ -654,20 +657,28 @@ void check_groups_of(const Problem& P, bool want_sparse, const char* what) {
     CHECK(dsm_destroy(ctx) == DSM_OK, "%s: destroy", what);
 }
 
-void check_groups() {
+void check_facts() {
     // On both sides of half-empty groups (8192 elements are 4 groups of a
     // chunk's 8), and tables with empty tensors, tails and full chunks.
     for (int layout : {DSM_REPLICAS_CONTIGUOUS, DSM_REPLICAS_BLOCKED, DSM_REPLICAS_STATE_BLOCKED}) {
-        const auto check = [&](std::vector<int64_t> ne, bool sparse, const char* what) {
+        const auto facts = [&](std::vector<int64_t> ne, bool sparse, const char* what) {
             for (int base : {DSM_BASE_ADAMW, DSM_BASE_SGD_MOMENTUM})
-                check_groups_of(Problem(ne, 2, 2, base, {}, layout), sparse, what);
+                check_facts_of(Problem(ne, 2, 2, base, {}, layout), sparse, true, what);
         };
-        check({8192}, true, "half the groups");
-        check({8193}, false, "one element past half");
-        check({8193, 6144}, true, "half the groups of two chunks");
-        check({8193, 6145}, false, "one group past half of two chunks");
-        check({1, 2047, 2048, 2049, 0, 16384, 0, 5, 16385, 40003, 1, 1, 1, 1, 1}, true, "ragged");
-        check({16384, 32769, 14337, 0, 16383}, false, "full chunks");
+        facts({8192}, true, "half the groups");
+        facts({8193}, false, "one element past half");
+        facts({8193, 6144}, true, "half the groups of two chunks");
+        facts({8193, 6145}, false, "one group past half of two chunks");
+        facts({1, 2047, 2048, 2049, 0, 16384, 0, 5, 16385, 40003, 1, 1, 1, 1, 1}, true, "ragged");
+        facts({16384, 32769, 14337, 0, 16383}, false, "full chunks");
+    }
+    // On both sides of 96 MiB of arenas: 5 copies of one worker's SGD, 10 of
+    // two workers' AdamW.
+    for (int64_t past : {0, 1}) {
+        check_facts_of(Problem({5033152 + past}, 1, 2, DSM_BASE_SGD_MOMENTUM), false, past == 0,
+                       "SGD, 96 MiB");
+        check_facts_of(Problem({2516544 + past}, 2, 2, DSM_BASE_ADAMW), false, past == 0,
+                       "AdamW, 96 MiB");
     }
 }
 
@@ -1477,7 +1488,7 @@ int main(int argc, char** argv) {
     check_local_map();
     check_layout_fuzz();
     check_init_and_chunks();
-    check_groups();
+    check_facts();
     check_chunk_search();
     check_round_end_waves();
     check_init_rejections();

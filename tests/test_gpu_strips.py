@@ -167,7 +167,7 @@ def test_mid_size_rounds_equal_per_worker_split_calls(numel, n, base, mode, layo
     against the same rounds by one local step call per worker and global steps
     with broadcast."""
     buffers = 4 if base == dsm.DSM_BASE_ADAMW else 3
-    assert 4 * sum(numel) * (2 + buffers * n) > 96 << 20
+    assert 4 * sum(numel) * (2 + buffers * n) > 96 << 20    # nontemporal kernels
     H, local, got = 2, LOCAL[base], []
     for fused in (True, False):
         ar = A.Arenas(numel, n, H, base, replica_layout=LAYOUTS[layout])

@@ -11,8 +11,9 @@ the whole C ABI runs without a GPU.  Its checks are:
   * the blocked layouts' addressing: every piece inside one block, and every
     element of every copy at its own slot of the allocation;
   * the randomized sign's bound words in the workspace;
-  * the strip groups that hold elements, as every launch is told of them, the
-    chunk table's group index and the search over it;
+  * the facts every launch is dispatched by (strip groups that hold elements,
+    whether the arenas stay in the caches), the chunk table's group index and
+    the search over it;
   * the Algorithm 1 state machine, with the layouts and map of each launch;
   * the replica source of each local launch, fresh or stale;
   * dsm_init_static: the static scratch, its limit, one context per device;

@@ -91,11 +91,11 @@ MUTATIONS = [
      "L->groups += c.len / dsm::kGroupElems;", "strip groups of a chunk rounded down"),
     ("int64_t(ctx->chunk0[i + 1] - ctx->chunk0[i]) * dsm::kSplit);",
      "int64_t(ctx->chunk0[i + 1] - ctx->chunk0[i]) * 0);", "no bound words counted"),
-    ("    if (dsm::sparse_chunks(L.groups, L.n_chunks))\n",
-     "    if (dsm::sparse_chunks(2 * L.groups, L.n_chunks))\n",
-     "sparse launches only up to a quarter full"),
-    ("        rep.sparse_groups = static_cast<uint32_t>(L.groups);",
-     "        rep.sparse_groups = static_cast<uint32_t>(L.groups - 1);", "one strip group too few"),
+    ("dsm::problem_facts(L.groups, L.n_chunks, 4 * copies * L.arena_elems);",
+     "dsm::problem_facts(L.groups, L.n_chunks, copies);", "every problem counted as cached"),
+    ("dsm::problem_facts(L.groups, L.n_chunks, 4 * copies * L.arena_elems);",
+     "dsm::problem_facts(L.groups - 1, L.n_chunks, 4 * copies * L.arena_elems);",
+     "one strip group too few"),
     ("(L.chunk0_off - L.bounds_off) / sizeof(int32_t), 0);",
      "(L.chunk0_off - L.bounds_off) / sizeof(int32_t), 7);", "bounds uploaded as 7"),
     ("    if (n_pieces * dsm::kBlockThreads >= (int64_t(1) << 32))",
