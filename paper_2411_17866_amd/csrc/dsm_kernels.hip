@@ -41,8 +41,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // 510 MB 344 against 317 us.  It pays for as long as the program's other kernels
 // leave room: 8 x 128K, n = 4, H = 4, the gradients written and a copy made
 // before each call, the round with all of that 101 us against 106 us without a
-// copy, 121 against 132 us with 32 MB read and written by it, 176 against 186 us
-// with 128 MB.  It costs once they fill the cache themselves, whose lines plain
+// copy, 121 against 132 us where it moves 32 MB, 176 against 186 us with 128 MB.  It costs once they fill the cache themselves, whose lines plain
 // accesses then displace and whose stores they wait for: 312 against 268 us with
 // 256 MB; after a 512 MB fill, local steps of 2M to 5M elements of all workers
 // take 16-20% longer.
