@@ -50,6 +50,27 @@ constexpr int even_waves(int n, int most) {
 constexpr int quad_strip_waves(int n, bool adamw) {
     return even_waves(n, adamw && n < kMaxRoundEndWaves ? 3 : 4);
 }
+// Whether the randomized round end over so many strip groups takes the four
+// strips of a bound word in a work-group, or clears the words (a launch of its
+// own, ~4 us) and raises them by atomic maxima, one strip per work-group.  The
+// round end from replicas with its second pass, one strip and four, us, at 8M,
+// 32M, 128M and 400M elements of all workers:
+//   SGD,   2 workers, contiguous    50  44 | 161 150 | 591 578 | 1819 1843
+//   SGD,   8 workers, contiguous    35  32 | 110 110 | 411 415 | 1244 1315
+//   SGD,   8 workers, state-blocked 35  33 | 105 110 | 377 404 | 1165 1251
+//   AdamW, 2 workers, contiguous    61  57 | 206 198 | 774 756 | 2373 2398
+//   AdamW, 8 workers, contiguous    50  45 | 162 158 | 614 610 | 1870 1922
+//   AdamW, 8 workers, state-blocked 51  46 | 162 157 | 585 581 | 1802 1796
+// The sides cross from 16M (SGD, state-blocked, five workers and more: up to 8%
+// from there on) to beyond 400M; the line is at 134M, 65536 strip groups times
+// workers.  SGD with three waves a strip (12 in a work-group, of which a CU
+// holds two and 8 waves stay idle) crosses at 16M: three workers, contiguous,
+// 45 45 | 137 148 | 499 571, five, state-blocked, 38 38 | 114 122 | 424 442, six
+// 37 35 | 111 115 | 407 422.
+constexpr bool takes_quads(int64_t groups, int n, bool adamw) {
+    const bool crosses_early = !adamw && (n == 3 || n == 5 || n == 6);
+    return n <= kMaxRoundEndWaves && groups * n < (crosses_early ? 8192 : 65536);
+}
 // Waves of the round end that takes one strip in a work-group.  SGD: 16; AdamW:
 // 8 (16 workers of 30M parameters: AdamW 65.3% (contiguous) and 72.6%
 // (state-blocked) of 8 TB/s with 16 waves, 68.0% and 75.4% with 8; SGD 73.9% and

@@ -1037,14 +1037,6 @@ constexpr bool round_end_groups_attainable() {
 }
 static_assert(round_end_groups_attainable(), "work-groups of the round end");
 
-// From here on the randomized round end clears the bound words and raises them
-// by atomic maxima, one strip per work-group; below, a work-group takes all
-// four strips of a word.  The four strips are slower (SGD, n = 16, 30M
-// parameters: 66% of 8 TB/s against 82%; AdamW, n = 4, 124M: 72% against 77%),
-// but the clearing is a launch of its own, ~4 us (3M parameters, n = 2: round
-// 81.6 us against 83.7 us).  In strip groups times workers, 134M elements.
-constexpr int64_t kAtomicBoundGroups = 65536;
-
 template <int BASE, int KIND, bool PIECE>
 static void launch_round_end_shape(const Chunk* chunks, int64_t n_chunks, const RoundEndArgs& a,
                                    hipStream_t st) {
@@ -1078,8 +1070,7 @@ static void launch_round_end_kind(const Chunk* chunks, int64_t n_chunks, const R
                                   hipStream_t st) {
     if constexpr (KIND == 2) {
         // A word's four strips keep 4 n KiB of step-H values in LDS.
-        if (a.gs.n <= kMaxRoundEndWaves &&
-            groups_of(n_chunks, a.rl) * a.gs.n < kAtomicBoundGroups) {
+        if (takes_quads(groups_of(n_chunks, a.rl), a.gs.n, BASE == kBaseAdamW)) {
             launch_round_end_shape<BASE, KIND, true>(chunks, n_chunks, a, st);
             return;
         }

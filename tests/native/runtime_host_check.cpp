@@ -706,6 +706,15 @@ void check_round_end_waves() {
             CHECK(waves <= most && waves <= n && (n + waves - 1) / waves == (n + most - 1) / most,
                   "%d workers on %d waves", n, waves);
         }
+    for (bool adamw : {false, true}) {
+        CHECK(dsm::takes_quads(65536 / 16 - 1, 16, adamw) && !dsm::takes_quads(65536 / 16, 16, adamw) &&
+                  !dsm::takes_quads(1, 17, adamw),
+              "work-groups of four strips");
+        CHECK(dsm::takes_quads(2730, 3, adamw) && dsm::takes_quads(2731, 3, adamw) == adamw &&
+                  dsm::takes_quads(1638, 5, adamw) && dsm::takes_quads(1639, 5, adamw) == adamw &&
+                  dsm::takes_quads(1365, 6, adamw) && dsm::takes_quads(1366, 6, adamw) == adamw,
+              "work-groups of four strips with three waves each");
+    }
     CHECK(dsm::strip_waves(9, true) == 5 && dsm::strip_waves(10, true) == 5 &&
               dsm::strip_waves(11, true) == 8 && dsm::strip_waves(17, false) == 9 &&
               dsm::strip_waves(20, false) == 10 && dsm::strip_waves(21, false) == 16 &&
