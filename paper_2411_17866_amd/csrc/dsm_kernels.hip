@@ -859,10 +859,19 @@ static_assert(attainable(kAdamWWaves) && attainable(kAdamWSharedWaves) && attain
               "waves of the local steps");
 // The global step loads n + 2 streams at once: n = 4, 80.3% with 8, 77% with
 // 12; n = 1, 81.0% with 12, 76% with 8.  n = 2 has 10 in one-wave work-groups
-// and 12 in those of four.
-constexpr int global_waves(int n) { return n == 1 ? 12 : n == 2 ? 10 : 8; }
-static_assert(attainable(global_waves(1)) && attainable(global_waves(2)) && attainable(global_waves(3)),
-              "waves of the global step");
+// and 12 in those of four.  Where n has no kernel of its own, four loads are in
+// flight at a time, and without the broadcast's stores 8 waves are too few: 100M
+// elements of all workers, n = 5, contiguous 140 us with 8, 119 us with 12 (the
+// kernel before 121 us), state-blocked 145 and 119 us; n = 3 165 and 141 us, n =
+// 9 105 and 94 us; n = 12 91 us with 8, 86 us with 10, 400M 338 us with 10, 349
+// us with 12.  From 16 workers on 8 again (n = 16, 400M, state-blocked 312 us
+// with 8, 323 us with 10), and with the broadcast at every n.
+constexpr int global_waves(int n, bool broadcast) {
+    if (n <= 2) return n == 1 ? 12 : 10;
+    if (broadcast || n == 4 || n == 8 || n >= 16) return 8;
+    return n < 10 ? 12 : 10;
+}
+static_assert(attainable(8) && attainable(10) && attainable(12), "waves of the global step");
 // The randomized first pass has no replica to write and lasts well with a few
 // more: n = 4 and 8, 80.7-81.8% with 12; n = 1 and 2, 79.6 and 83.3% with 16.
 constexpr int pass1_waves(int n) { return n <= 2 ? 16 : 12; }
@@ -1159,12 +1168,12 @@ static void launch_global_det_n(const Chunk* chunks, int64_t n_chunks, float* x,
                                 int map, hipStream_t st) {
     if (rl.cached()) {
         launch_strips(k_global_det<0, RULE, BCAST, kCached>, chunks, n_chunks, rl, map, sc.n + 2,
-                      global_waves(sc.n), st, x, m, v, x_rep, rl, sc);
+                      global_waves(sc.n, BCAST), st, x, m, v, x_rep, rl, sc);
         return;
     }
 #define DSM_GLOBAL_DET(NW)                                                                       \
     launch_strips(k_global_det<NW, RULE, BCAST, kStream>, chunks, n_chunks, rl, map, sc.n + 2,            \
-                  global_waves(sc.n), st, x, m, v, x_rep, rl, sc)
+                  global_waves(sc.n, BCAST), st, x, m, v, x_rep, rl, sc)
     switch (sc.n) {
         case 1: DSM_GLOBAL_DET(1); break;
         case 2: DSM_GLOBAL_DET(2); break;
