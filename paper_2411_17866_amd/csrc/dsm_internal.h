@@ -66,9 +66,12 @@ constexpr int quad_strip_waves(int n, bool adamw) {
 // workers.  SGD with three waves a strip (12 in a work-group, of which a CU
 // holds two and 8 waves stay idle) crosses at 16M: three workers, contiguous,
 // 45 45 | 137 148 | 499 571, five, state-blocked, 38 38 | 114 122 | 424 442, six
-// 37 35 | 111 115 | 407 422.
+// 37 35 | 111 115 | 407 422.  So does AdamW with 10 workers and more, whose
+// three waves a strip then take four turns and more: 14 workers at 16M, 24M, 64M
+// and 130M, contiguous, 84 84 | 119 123 | 293 308 | 581 621, state-blocked 84 84 |
+// 112 122 | 277 301 | 547 596.
 constexpr bool takes_quads(int64_t groups, int n, bool adamw) {
-    const bool crosses_early = !adamw && (n == 3 || n == 5 || n == 6);
+    const bool crosses_early = adamw ? n >= 10 : n == 3 || n == 5 || n == 6;
     return n <= kMaxRoundEndWaves && groups * n < (crosses_early ? 8192 : 65536);
 }
 // Waves of the round end that takes one strip in a work-group.  SGD: 16; AdamW:

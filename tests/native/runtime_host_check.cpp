@@ -707,9 +707,13 @@ void check_round_end_waves() {
                   "%d workers on %d waves", n, waves);
         }
     for (bool adamw : {false, true}) {
-        CHECK(dsm::takes_quads(65536 / 16 - 1, 16, adamw) && !dsm::takes_quads(65536 / 16, 16, adamw) &&
-                  !dsm::takes_quads(1, 17, adamw),
+        CHECK(dsm::takes_quads(65536 / 8 - 1, 8, adamw) && !dsm::takes_quads(65536 / 8, 8, adamw) &&
+                  dsm::takes_quads(1, 16, adamw) && !dsm::takes_quads(1, 17, adamw),
               "work-groups of four strips");
+        CHECK(dsm::takes_quads(819, 10, adamw) && dsm::takes_quads(820, 10, adamw) == !adamw &&
+                  dsm::takes_quads(7281, 9, adamw) && !dsm::takes_quads(7282, 9, adamw) &&
+                  dsm::takes_quads(511, 16, adamw) && dsm::takes_quads(512, 16, adamw) == !adamw,
+              "work-groups of four strips, many workers");
         CHECK(dsm::takes_quads(2730, 3, adamw) && dsm::takes_quads(2731, 3, adamw) == adamw &&
                   dsm::takes_quads(1638, 5, adamw) && dsm::takes_quads(1639, 5, adamw) == adamw &&
                   dsm::takes_quads(1365, 6, adamw) && dsm::takes_quads(1366, 6, adamw) == adamw,

@@ -162,6 +162,8 @@ DENSE_MID = [20_000_003, 5, 16_385]     # strip groups: 9 whole turns of 1024 an
     (DENSE_MID, 6, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0),
     (DENSE_MID, 3, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 1),
     (DENSE_MID, 2, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 0),
+    ([2_000_003, 5, 16_385], 10, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_FLIP, 2),
+    ([1_500_007, 16_384], 10, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_RAND_ZERO, 0),
 ])
 def test_mid_size_rounds_equal_per_worker_split_calls(numel, n, base, mode, layout):
     """Two lazy rounds of H = 2 by all-worker local steps and fused round ends
