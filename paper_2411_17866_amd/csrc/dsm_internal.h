@@ -278,6 +278,14 @@ inline int local_map(int64_t n_chunks, int n_workers, int map) {
     return map;
 }
 
+// The workers that one launch of the step from x takes: all n, or where their
+// row is too long for the map, a half, a quarter and so on of them.
+inline int workers_per_row(int64_t n_chunks, int n, int map) {
+    int per = n;
+    while (per > 1 && local_map(n_chunks, per, map) != map) per = (per + 1) / 2;
+    return per;
+}
+
 // Kernel launchers (dsm_kernels.hip).  All return the launch status.  The
 // replica buffer x_rep is addressed through its RepLayout rl, and g_rep, s1
 // and s2 through the layouts of ml; map is the launch's map.

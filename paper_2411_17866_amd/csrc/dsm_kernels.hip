@@ -999,8 +999,9 @@ hipError_t launch_local_sgdm(const Chunk* chunks, int64_t n_chunks, float* x_rep
 
 // Local step of every worker when every replica is stale (after a global step
 // without broadcast): each worker starts from the global model.  The workers
-// are interleaved, so that x is read from HBM once for all of them (and per
-// worker in the rare launch whose row is too long to interleave).  One wave
+// are interleaved, so that x is read from HBM once for all of them, or for as
+// many as fit a row (12 workers of 1.45G elements, SGD: two launches of six take
+// 44.2 ms, one launch with x read for each worker 54.0 ms).  One wave
 // taking all n steps of a strip, with its 3 n + 1 streams at a time, ran at
 // 66.1% (small, n = 8, state-blocked) and 67.5% (n = 4, contiguous) of 8 TB/s
 // over the same bytes; this at 83.1% and 80%.
@@ -1010,15 +1011,19 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
                                const AdamScalars& as, const SgdScalars& ss, int map,
                                hipStream_t st) {
     if (n_chunks == 0) return hipSuccess;
-    map = local_map(n_chunks, n, map);
-    if (adamw)
-        launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kShared>, chunks, n_chunks,
-                     rl, map, 4, kAdamWSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1,
-                     s2, ml, 0, n, as);
-    else
-        launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kShared>, chunks, n_chunks,
-                     rl, map, 3, kSgdSharedWaves, n, st, x_rep, rl, x, single_copy(), g_rep, s1, ml,
-                     0, n, ss);
+    const int per = workers_per_row(n_chunks, n, map);
+    map = local_map(n_chunks, per, map);
+    for (int w0 = 0; w0 < n; w0 += per) {
+        const int nw = per < n - w0 ? per : n - w0;
+        if (adamw)
+            launch_local(rl.cached() ? k_local_adamw<kCached> : k_local_adamw<kShared>, chunks,
+                         n_chunks, rl, map, 4, kAdamWSharedWaves, nw, st, x_rep, rl, x,
+                         single_copy(), g_rep, s1, s2, ml, w0, nw, as);
+        else
+            launch_local(rl.cached() ? k_local_sgdm<kCached> : k_local_sgdm<kShared>, chunks,
+                         n_chunks, rl, map, 3, kSgdSharedWaves, nw, st, x_rep, rl, x,
+                         single_copy(), g_rep, s1, ml, w0, nw, ss);
+    }
     return hipGetLastError();
 }
 

@@ -114,7 +114,7 @@ dsm_status check_problem(const dsm_problem* p) {
 // when the replicas are blocked).  The workspace holds, each part at a 256-byte boundary: the chunk table
 // (kChunkElems elements per chunk, never crossing a tensor); the per-tensor
 // bound words; the first chunk of each tensor (n_tensors + 1 words); and one
-// piece-maximum word per work-group piece (n_chunks * kSplit), level one of
+// word for each four strips (n_chunks * kSplit), level one of
 // the bound.
 dsm_status make_layout(const dsm_problem* p, Layout* L, std::vector<dsm::Chunk>* chunks,
                        std::vector<int32_t>* chunk0 = nullptr) {

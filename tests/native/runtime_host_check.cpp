@@ -1413,6 +1413,22 @@ void check_local_map() {
             CHECK(dsm::local_map(1LL << 40, n, il) == base, "huge row falls back");
         }
     }
+    // The step from x halves the workers of a launch until their row fits.
+    for (int n : {1, 2, 3, 12, 63, 64}) {
+        for (int64_t n_chunks : {int64_t(1), int64_t(17000), int64_t(88501), int64_t(600000),
+                                 int64_t(1048574)}) {
+            const int per = dsm::workers_per_row(n_chunks, n, kInterleaveWorkers);
+            const bool fits = n_chunks * kSplit * per < limit;
+            CHECK(per >= 1 && per <= n && fits, "%lld chunks, %d workers: %d a launch",
+                  static_cast<long long>(n_chunks), n, per);
+            CHECK(per == n || n_chunks * kSplit * (2 * per) >= limit ||
+                      n_chunks * kSplit * (2 * per - 1) >= limit,
+                  "%lld chunks, %d workers: no more than a half too few",
+                  static_cast<long long>(n_chunks), n);
+            CHECK(dsm::workers_per_row(n_chunks, n, 0) == n, "no row, no split");
+        }
+    }
+    CHECK(dsm::workers_per_row(88501, 12, kInterleaveWorkers) == 6, "12 workers of 1.45G elements");
     // The state-blocked layout's default local map interleaves the workers.
     CHECK(dsm::kMapsByLayout[DSM_REPLICAS_STATE_BLOCKED].local & kInterleaveWorkers,
           "state-blocked local steps interleave workers");

@@ -151,6 +151,7 @@ def test_large_randomized_round_end_equals_split(layout):
 
 SPARSE_MID = [(k * 7919) % 9_973 + 1 for k in range(400)] + [1_000_003]    # 3M elements
 SPARSE_LARGE = [(k * 2741) % 4095 + 2 for k in range(16_000)]              # 33M
+MANY_CHUNKS = [40] * 17_000   # with 64 workers more strips than a grid row holds
 DENSE_MID = [20_000_003, 5, 16_385]     # strip groups: 9 whole turns of 1024 and a part
 
 
@@ -159,6 +160,7 @@ DENSE_MID = [20_000_003, 5, 16_385]     # strip groups: 9 whole turns of 1024 an
     (SPARSE_MID, 6, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 1),
     (SPARSE_LARGE, 3, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0),
     (SPARSE_LARGE, 3, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 2),
+    (MANY_CHUNKS, 64, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_DET, 0),
     (DENSE_MID, 6, dsm.DSM_BASE_ADAMW, dsm.DSM_SIGN_DET, 0),
     (DENSE_MID, 3, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_ZERO, 1),
     (DENSE_MID, 2, dsm.DSM_BASE_SGD_MOMENTUM, dsm.DSM_SIGN_RAND_FLIP, 0),
