@@ -1035,14 +1035,15 @@ hipError_t launch_local_from_x(const Chunk* chunks, int64_t n_chunks, const floa
 // streams a wave and has little arithmetic: swept 4 to 32 at 8M to 400M elements
 // of all workers, deterministic, both from x and from replicas; 25M, contiguous,
 // from x, with AdamW's counts and with its own: one worker 125 and 117 us, two 92
-// and 84 us, three 86 and 74 us, four 76 and 67 us, five 76 and 67 us.  From
-// eight waves a group on, the 32 waves that a CU holds are the limit, but not the
-// LDS: waves that are done make room for the next group's while the first of
-// theirs takes the global step.
+// and 84 us, three 86 and 74 us, four 76 and 67 us, five 76 and 67 us; eight at
+// 2.8G from replicas 8.4 and 7.8 ms with 4 and 5.  From eight waves a group on,
+// the 32 waves that a CU holds are the limit, but not the LDS: waves that are
+// done make room for the next group's while the first of theirs takes the global
+// step.  16 waves again 4 (2.8G, contiguous, 8.0 ms, 8.2 ms with 5).
 constexpr int round_end_groups(int waves, bool randomized, bool adamw) {
     if (!adamw) {
-        constexpr int sgd[] = {16, 12, 10, 8, 6};
-        return waves <= 5 ? sgd[waves - 1] : 5;
+        constexpr int sgd[] = {16, 12, 10, 8, 6, 5, 5, 5};
+        return waves <= 8 ? sgd[waves - 1] : randomized ? 5 : 4;
     }
     const int groups = waves == 1 ? 12 : waves == 2 ? 8 : waves == 3 ? 6 : waves == 4 ? 5 : 4;
     return groups + (randomized ? (waves == 1 ? 2 : 1) : 0);
