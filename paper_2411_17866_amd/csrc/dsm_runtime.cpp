@@ -541,9 +541,9 @@ dsm_status dsm_local_step(dsm_ctx* ctx, int32_t worker, int64_t step, const dsm_
     }
     // Workers whose replica is stale read the global model (the
     // synchronisation step folded into their first local step).  When every
-    // worker steps and every replica is stale, one launch reads x once for all
-    // of them; otherwise one launch per run of consecutive workers with the
-    // same source.
+    // worker steps and every replica is stale, x is read once for all of them
+    // (or for as many as fit a grid row); otherwise one launch per run of
+    // consecutive workers with the same source.
     bool all_stale = worker < 0 && ctx->n > 1;
     for (int i = 0; i < ctx->n && all_stale; ++i) all_stale = ctx->stale[i] != 0;
     if (all_stale) {
